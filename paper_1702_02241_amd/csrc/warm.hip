@@ -3,15 +3,16 @@
 // between full and low resolution.  The declarations and the definitions of
 // every quantity are in rpca_warm.h.
 //
-// GEMM.  C = op(A) op(B) with op = identity or transpose, row-major storage,
-// 64 x 64 output tiles per 256-thread workgroup (four waves of 32 x 32, each
-// four 16x16 v_mfma_f32_16x16x4f32 accumulators), K staged through LDS in
-// slices of 16.  Loads are coalesced along whichever index is contiguous in
-// memory.  When the output has too few tiles to fill the chip (the 512-wide
-// hidden layer against a K of 10^4 .. 10^5) K is split across workgroups
-// and the partials are summed in a fixed order by a second kernel, so every
-// result is bitwise reproducible.  The epilogue adds a bias, applies ReLU or
-// gates by a previous activation (the ReLU derivative in the backward pass).
+// GEMM.  C = op(A) op(B) with op = identity or transpose, row-major storage, one
+// 64 x 64 output tile per wave (4 x 4 accumulators of v_mfma_f32_16x16x4f32).  The
+// operands go from memory to registers as 16-byte loads and straight into the
+// matrix unit, one block of 16 K values ahead of the products: no LDS staging and
+// no barrier in the K loop.  When the output has few tiles K is split over the
+// waves of a workgroup (summed through LDS) and over workgroups (partials summed
+// by a second kernel), always in a fixed order, so every result is bitwise
+// reproducible.  The epilogue adds a bias, applies ReLU or gates by a previous
+// activation (the ReLU derivative in the backward pass).  At most four rows
+// (one window's prediction) take a matrix-vector kernel instead.
 
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -28,8 +29,11 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 
 constexpr int GT = 256;
 constexpr int BM = 64, BN = 64, BK = 16;
-constexpr int LPAD = 4;
 constexpr int KMAX_LOSS = 32;
+
+// 16-byte accesses at any 4-byte aligned address (rows of odd length)
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef double d4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ f4 mfma_f32(float a, float b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -41,7 +45,7 @@ struct GemmArgs {
   float* C;
   int64_t M, N, K;
   int64_t lda, ldb, ldc;
-  int64_t kchunk;       // K range per split (multiple of BK)
+  int64_t kchunk;       // K range per wave of a split (multiple of BK)
   const float* bias;    // N values or null
   const float* gate;    // M x N (leading dimension ldg) or null: C = acc * (gate > 0)
   int64_t ldg;
@@ -56,95 +60,252 @@ __device__ __forceinline__ float epilogue(const GemmArgs& a, int64_t i, int64_t 
   return v;
 }
 
-template <bool TA, bool TB>
+// One operand's 16 values of a K block: o[t][q] is element (16-wide tile t, K = k0 + 4 lk + q)
+// of this lane.  K order and the order of a tile's rows are free as long as both
+// operands and the output agree, so every load is 16 contiguous bytes:
+//   KMAJ (element (x, k) at p[k ld + x]): row k, x = x0 + 4 li + t -- tile t holds x0 + 4 i + t
+//   else (p[x ld + k]): row x = x0 + 16 t + li, four K values -- tile t holds x0 + 16 t + i
+// Elements past X or kend read as zero.
+template <bool KMAJ>
+__device__ __forceinline__ void load_operand(const float* __restrict__ p, int64_t ld, int64_t x0, int64_t X, int64_t k0,
+                                             int64_t kend, int li, int lk, float (&o)[4][4]) {
+  if (KMAJ) {
+    if (x0 + 64 <= X && k0 + BK <= kend) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f4 v = *reinterpret_cast<const f4u*>(p + (k0 + 4 * lk + q) * ld + x0 + 4 * li);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) o[t][q] = v[t];
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int64_t k = k0 + 4 * lk + q, x = x0 + 4 * li + t;
+          o[t][q] = (k < kend && x < X) ? p[k * ld + x] : 0.f;
+        }
+    }
+  } else {
+    if (x0 + 64 <= X && k0 + BK <= kend) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const f4 v = *reinterpret_cast<const f4u*>(p + (x0 + 16 * t + li) * ld + k0 + 4 * lk);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[t][q] = v[q];
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int64_t k = k0 + 4 * lk + q, x = x0 + 16 * t + li;
+          o[t][q] = (k < kend && x < X) ? p[x * ld + k] : 0.f;
+        }
+    }
+  }
+}
+
+// FP32 MFMA-bound (64 products of 32 cycles per 16 loads of a lane): 64 x 64 a wave makes
+// each 16-byte load feed 16 products.  At 64 rows of the 9700-512-49000 network: y = h W2
+// 91 -> 59 us, dz = dy W2^T 158 -> 70 us, dW2 = h^T dy 70 -> 53 us against a 64 x 64
+// workgroup tile staged through LDS with two barriers per 16 K values; the products alone
+// are 20 us each at the matrix unit's rate.
+//
+// op(A) is KMAJ when TA, op(B) when !TB.  WK = 4: the workgroup's waves split the K range
+// of one tile and meet in LDS; WK = 1 (K of a few blocks): each wave has its own tile.
+template <bool TA, bool TB, int WK>
 __global__ __launch_bounds__(GT) void k_gemm(GemmArgs a) {
-  __shared__ float As[BK][BM + LPAD];  // As[kk][mm] = op(A)[m0 + mm][k0 + kk]
-  __shared__ float Bs[BK][BN + LPAD];  // Bs[kk][nn] = op(B)[k0 + kk][n0 + nn]
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wm = w >> 1, wn = w & 1;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4;
-  const int64_t m0 = (int64_t)blockIdx.y * BM, n0 = (int64_t)blockIdx.x * BN;
-  const int64_t kbeg = (int64_t)blockIdx.z * a.kchunk;
+  const int64_t m0 = (int64_t)blockIdx.y * BM, n0 = ((int64_t)blockIdx.x * (WK == 1 ? 4 : 1) + (WK == 1 ? w : 0)) * BN;
+  const int64_t kbeg = ((int64_t)blockIdx.z * WK + (WK == 1 ? 0 : w)) * a.kchunk;
   int64_t kend = kbeg + a.kchunk;
   if (kend > a.K) kend = a.K;
-  f4 acc[2][2];
+  if (WK == 1 && n0 >= a.N) return;
+  f4 acc[4][4];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < 4; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
 
-  for (int64_t k0 = kbeg; k0 < kend; k0 += BK) {
-#pragma unroll
-    for (int r = 0; r < (BM * BK) / GT; ++r) {
-      const int idx = tid + GT * r;
-      const int mm = TA ? (idx & (BM - 1)) : (idx >> 4);
-      const int kk = TA ? (idx >> 6) : (idx & (BK - 1));
-      const int64_t gm = m0 + mm, gk = k0 + kk;
-      float v = 0.f;
-      if (gm < a.M && gk < kend) v = TA ? a.A[gk * a.lda + gm] : a.A[gm * a.lda + gk];
-      As[kk][mm] = v;
-    }
-#pragma unroll
-    for (int r = 0; r < (BN * BK) / GT; ++r) {
-      const int idx = tid + GT * r;
-      const int nn = TB ? (idx >> 4) : (idx & (BN - 1));
-      const int kk = TB ? (idx & (BK - 1)) : (idx >> 6);
-      const int64_t gn = n0 + nn, gk = k0 + kk;
-      float v = 0.f;
-      if (gn < a.N && gk < kend) v = TB ? a.B[gn * a.ldb + gk] : a.B[gk * a.ldb + gn];
-      Bs[kk][nn] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int ks = 0; ks < BK; ks += 4) {
-      float av[2], bv[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) av[i] = As[ks + lk][wm * 32 + i * 16 + li];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) bv[j] = Bs[ks + lk][wn * 32 + j * 16 + li];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = mfma_f32(av[i], bv[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-  // lane holds rows 4*lk + r, column li of each 16x16 block
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t gm = m0 + wm * 32 + i * 16 + 4 * lk + r;
-        const int64_t gn = n0 + wn * 32 + j * 16 + li;
-        if (gm < a.M && gn < a.N) {
-          const float v = acc[i][j][r];
-          if (a.part)
-            a.part[(int64_t)blockIdx.z * a.M * a.N + gm * a.N + gn] = v;
-          else
-            a.C[gm * a.ldc + gn] = epilogue(a, gm, gn, v);
-        }
+  if (kbeg < kend) {
+    float av[4][4], bv[4][4];
+    load_operand<TA>(a.A, a.lda, m0, a.M, kbeg, kend, li, lk, av);
+    load_operand<!TB>(a.B, a.ldb, n0, a.N, kbeg, kend, li, lk, bv);
+    for (int64_t k0 = kbeg; k0 < kend; k0 += BK) {
+      float an[4][4], bn[4][4];
+      const bool more = k0 + BK < kend;
+      if (more) {
+        load_operand<TA>(a.A, a.lda, m0, a.M, k0 + BK, kend, li, lk, an);
+        load_operand<!TB>(a.B, a.ldb, n0, a.N, k0 + BK, kend, li, lk, bn);
       }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[i][j] = mfma_f32(av[i][q], bv[j][q], acc[i][j]);
+      if (more) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            av[i][q] = an[i][q];
+            bv[i][q] = bn[i][q];
+          }
+      }
+    }
+  }
+  // lane holds rows 4 lk + r, column li of each 16 x 16 tile (i, j)
+  auto row = [&](int i, int r) -> int64_t { return m0 + (TA ? 4 * (4 * lk + r) + i : 16 * i + 4 * lk + r); };
+  auto put = [&](int i, int r, const f4& v) {  // v[j]: the four N tiles
+    const int64_t gm = row(i, r);
+    if (gm >= a.M) return;
+    float* dst = a.part ? a.part + (int64_t)blockIdx.z * a.M * a.N + gm * a.N : a.C + gm * a.ldc;
+    const int64_t gn = n0 + (TB ? li : 4 * li);
+    if (!TB && gn + 4 <= a.N) {
+      f4 o = v;
+      if (!a.part)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = epilogue(a, gm, gn + j, v[j]);
+      *reinterpret_cast<f4u*>(dst + gn) = o;
+      return;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int64_t g = gn + (TB ? 16 * j : j);
+      if (g < a.N) dst[g] = a.part ? v[j] : epilogue(a, gm, g, v[j]);
+    }
+  };
+  if (WK == 1) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) put(i, r, f4{acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]});
+  } else {
+    // wave w finishes the row tile i = w: the others' accumulators of it through LDS,
+    // added in wave order
+    __shared__ f4 sP[4][4][4][64];  // [row tile][wave][j][lane]
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) sP[i][w][j][lane] = acc[i][j];
+    __syncthreads();
+    f4 s[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s[j] = ((sP[w][0][j][lane] + sP[w][1][j][lane]) + sP[w][2][j][lane]) + sP[w][3][j][lane];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) put(w, r, f4{s[0][r], s[1][r], s[2][r], s[3][r]});
+  }
 }
 
 __global__ __launch_bounds__(GT) void k_splitk_reduce(GemmArgs a, int splits) {
   const int64_t mn = a.M * a.N;
   for (int64_t o = (int64_t)blockIdx.x * GT + threadIdx.x; o < mn; o += (int64_t)gridDim.x * GT) {
     float s = 0.f;
-    for (int z = 0; z < splits; ++z) s += a.part[(int64_t)z * mn + o];
+    int z = 0;
+    for (; z + 7 < splits; z += 8) {  // eight loads in flight, added in order
+      float x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = a.part[(int64_t)(z + e) * mn + o];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s += x[e];
+    }
+    for (; z < splits; ++z) s += a.part[(int64_t)z * mn + o];
     const int64_t i = o / a.N, j = o % a.N;
     a.C[i * a.ldc + j] = epilogue(a, i, j, s);
   }
 }
 
-// out[j] = sum over rows of A (rows x cols, row-major), fixed order
-__global__ __launch_bounds__(GT) void k_colsum(const float* A, int64_t rows, int64_t cols, float* out) {
+// C = A B for at most MV rows of A (row-major, B K-major: the forward pass of one or a few
+// windows).  Memory-bound on B (100 MB of W2 in 21.6 us, 4.6 TB/s; the 64-row tile took
+// 68 us, padding one row to 64): a workgroup of 32 lane columns (VEC values each) x 32 K
+// groups streams its K range once, the groups' sums meet in LDS in group order.
+constexpr int MV = 4, MV_T = 1024, MV_L = 32, MV_G = MV_T / MV_L, MV_K = 512;
+template <int VEC>
+__global__ __launch_bounds__(MV_T) void k_gemv(GemmArgs a) {
+  __shared__ float sx[MV][MV_K];
+  __shared__ float sp[MV_G][MV_L * VEC];
+  const int tid = threadIdx.x, c = tid & (MV_L - 1), gk = tid / MV_L;
+  const int M = (int)a.M;
+  const int64_t n = ((int64_t)blockIdx.x * MV_L + c) * VEC;
+  const int64_t kbeg = (int64_t)blockIdx.z * a.kchunk;
+  const int64_t kend = kbeg + a.kchunk < a.K ? kbeg + a.kchunk : a.K;
+  float acc[MV][VEC] = {};
+  for (int64_t k0 = kbeg; k0 < kend; k0 += MV_K) {
+    const int nk = (int)(kend - k0 < MV_K ? kend - k0 : MV_K);
+    __syncthreads();
+    for (int e = tid; e < M * MV_K; e += MV_T) {
+      const int b = e / MV_K, kk = e % MV_K;
+      if (kk < nk) sx[b][kk] = a.A[b * a.lda + k0 + kk];
+    }
+    __syncthreads();
+    if (n < a.N) {
+#pragma unroll 8
+      for (int kk = gk; kk < nk; kk += MV_G) {
+        const float* src = a.B + (k0 + kk) * a.ldb + n;
+        float v[VEC];
+        if (VEC == 4) {
+          const f4 x = *reinterpret_cast<const f4*>(src);
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) v[e] = x[e & 3];
+        } else {
+          v[0] = src[0];
+        }
+#pragma unroll
+        for (int b = 0; b < MV; ++b)
+          if (b < M)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) acc[b][e] = fmaf(sx[b][kk], v[e], acc[b][e]);
+      }
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < MV; ++b) {
+    if (b >= M) break;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) sp[gk][c * VEC + e] = acc[b][e];
+    __syncthreads();
+    const int64_t j = (int64_t)blockIdx.x * MV_L * VEC + tid;
+    if (tid < MV_L * VEC && j < a.N) {
+      float s = 0.f;
+#pragma unroll
+      for (int q = 0; q < MV_G; ++q) s += sp[q][tid];
+      if (a.part)
+        a.part[(int64_t)blockIdx.z * a.M * a.N + b * a.N + j] = s;
+      else
+        a.C[b * a.ldc + j] = epilogue(a, b, j, s);
+    }
+  }
+}
+
+// out[j] = sum over rows of A (rows x cols, row-major), added in row order; two
+// matrices in one launch (blockIdx.y)
+struct ColsumArgs {
+  const float* A[2];
+  int64_t rows, cols[2];
+  float* out[2];
+};
+__global__ __launch_bounds__(GT) void k_colsum(ColsumArgs a) {
+  const int y = blockIdx.y;
+  const float* __restrict__ A = a.A[y];
+  const int64_t cols = a.cols[y], rows = a.rows;
   const int64_t j = (int64_t)blockIdx.x * GT + threadIdx.x;
   if (j >= cols) return;
   float s = 0.f;
-  for (int64_t r = 0; r < rows; ++r) s += A[r * cols + j];
-  out[j] = s;
+  int64_t r = 0;
+  for (; r + 15 < rows; r += 16) {  // sixteen loads in flight
+    float x[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) x[e] = A[(r + e) * cols + j];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) s += x[e];
+  }
+  for (; r < rows; ++r) s += A[r * cols + j];
+  a.out[y][j] = s;
 }
 
 // ---------------------------------------------------------------------------
@@ -154,71 +315,117 @@ __global__ __launch_bounds__(GT) void k_colsum(const float* A, int64_t rows, int
 //   Gvv = Vh^T Vh, Mtv = TV^T Vh, Gtv = TV^T TV  (k x k, over the nv rows)
 //   ||Uh Vh^T - TU TV^T||^2 = <Guu, Gvv> - 2 <Mtu, Mtv> + <Gtu, Gtv>
 //   d/dUh = 2 (Uh Gvv - TU Mtv),   d/dVh = 2 (Vh Guu - TV Mtu).
-// k_loss_grams: one block per batch element, rows staged through LDS; the
-// six matrices go to grams[b][6][k][k] (FP64).
-__global__ __launch_bounds__(GT) void k_loss_grams(const float* y, const float* TU, const float* TV,
-                                                   int mu, int nv, int k, int64_t d_out,
-                                                   double* grams) {
-  constexpr int ROWS = 64;
-  __shared__ float sP[ROWS * KMAX_LOSS];
-  __shared__ float sT[ROWS * KMAX_LOSS];
-  const int b = blockIdx.x, tid = threadIdx.x;
-  const int kk2 = k * k;
-  const float* yb = y + (int64_t)b * d_out;
-  double* gb = grams + (int64_t)b * 6 * kk2;
-  for (int side = 0; side < 2; ++side) {
-    const int rows = side == 0 ? mu : nv;
-    const float* P = side == 0 ? yb : yb + (int64_t)mu * k;
-    const float* T = side == 0 ? TU + (int64_t)b * mu * k : TV + (int64_t)b * nv * k;
-    double aPP[4] = {0, 0, 0, 0}, aTP[4] = {0, 0, 0, 0}, aTT[4] = {0, 0, 0, 0};
-    for (int r0 = 0; r0 < rows; r0 += ROWS) {
-      const int nr = rows - r0 < ROWS ? rows - r0 : ROWS;
-      __syncthreads();
-      for (int idx = tid; idx < nr * k; idx += GT) {
-        sP[idx] = P[(int64_t)r0 * k + idx];
-        sT[idx] = T[(int64_t)r0 * k + idx];
-      }
-      __syncthreads();
+// All of it in FP64 on v_mfma_f64_16x16x4f64 (KB = 1: k <= 16, 2: k <= 32).  One FP64
+// lane layout serves both kernels: A and B operands hold row / column li at K = lk, the
+// output holds rows 4 r + lk, column li.
+//
+// k_loss_grams: a workgroup takes one row chunk of one batch element, its waves
+// interleaved groups of four rows, four of them in flight (64 windows of 4900 rows: 19 us; one workgroup per
+// window with one thread per entry took 367 us); the waves' sums meet in LDS in wave order and the
+// chunk's three matrices go to gpart[b][chunk][3][k][k].  Chunks [0, cu) cover the
+// mu rows of U, [cu, cu + cv) the nv rows of V.
+struct LossArgs {
+  const float* y;
+  const float* TU;
+  const float* TV;
+  int mu, nv, k, batch;
+  int per, cu, cv;  // rows per chunk, chunks of each side
+  int64_t d_out;
+  double* gpart;
+  double* grams;  // [batch][6][k][k]
+  double* lossb;  // [batch]
+  double* loss;
+  float* dy;
+};
+
+__device__ __forceinline__ d4 mfma_f64(double a, double b, d4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+template <int KB>
+__global__ __launch_bounds__(GT) void k_loss_grams(LossArgs a) {
+  constexpr int NTL = 3 * KB * KB;
+  __shared__ double sG[GT / 64][NTL * 256];
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int b = blockIdx.y, ch = blockIdx.x, k = a.k;
+  const bool us = ch < a.cu;
+  const int rows = us ? a.mu : a.nv, r0 = (us ? ch : ch - a.cu) * a.per;
+  const int r1 = r0 + a.per < rows ? r0 + a.per : rows;
+  const float* P = a.y + (int64_t)b * a.d_out + (us ? 0 : (int64_t)a.mu * k);
+  const float* T = us ? a.TU + (int64_t)b * a.mu * k : a.TV + (int64_t)b * a.nv * k;
+  d4 acc[3][KB][KB];
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int e = tid + GT * s;
-        if (e < kk2) {
-          const int p = e / k, q = e % k;
-          double pp = 0, tp = 0, tt = 0;
-          for (int i = 0; i < nr; ++i) {
-            const double up = sP[i * k + p], uq = sP[i * k + q], tpv = sT[i * k + p], tq = sT[i * k + q];
-            pp += up * uq;
-            tp += tpv * uq;
-            tt += tpv * tq;
-          }
-          aPP[s] += pp;
-          aTP[s] += tp;
-          aTT[s] += tt;
+  for (int m = 0; m < 3; ++m)
+#pragma unroll
+    for (int i = 0; i < KB; ++i)
+#pragma unroll
+      for (int j = 0; j < KB; ++j) acc[m][i][j] = d4{0., 0., 0., 0.};
+  constexpr int UN = 4;  // groups of rows whose loads are in flight together
+  for (int rb = r0 + 4 * w; rb < r1; rb += 16 * UN) {
+    float pv[UN][KB], tv[UN][KB];
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+#pragma unroll
+      for (int i = 0; i < KB; ++i) {
+        const int r = rb + 16 * u + lk, c = 16 * i + li;
+        const bool ok = r < r1 && c < k;
+        const int64_t o = ok ? (int64_t)r * k + c : 0;
+        pv[u][i] = P[o];
+        tv[u][i] = T[o];
+        pv[u][i] = ok ? pv[u][i] : 0.f;
+        tv[u][i] = ok ? tv[u][i] : 0.f;
+      }
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+#pragma unroll
+      for (int i = 0; i < KB; ++i)
+#pragma unroll
+        for (int j = 0; j < KB; ++j) {
+          const double p = pv[u][i], t = tv[u][i], q = pv[u][j], v = tv[u][j];
+          acc[0][i][j] = mfma_f64(p, q, acc[0][i][j]);
+          acc[1][i][j] = mfma_f64(t, q, acc[1][i][j]);
+          acc[2][i][j] = mfma_f64(t, v, acc[2][i][j]);
         }
-      }
-    }
+  }
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int e = tid + GT * s;
-      if (e < kk2) {
-        gb[(3 * side + 0) * kk2 + e] = aPP[s];
-        gb[(3 * side + 1) * kk2 + e] = aTP[s];
-        gb[(3 * side + 2) * kk2 + e] = aTT[s];
-      }
-    }
+  for (int m = 0; m < 3; ++m)
+#pragma unroll
+    for (int i = 0; i < KB; ++i)
+#pragma unroll
+      for (int j = 0; j < KB; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sG[w][((m * KB + i) * KB + j) * 256 + (4 * r + lk) * 16 + li] = acc[m][i][j][r];
+  __syncthreads();
+  const int kk2 = k * k;
+  double* out = a.gpart + ((int64_t)b * (a.cu + a.cv) + ch) * 3 * kk2;
+  for (int e = threadIdx.x; e < 3 * kk2; e += GT) {
+    const int m = e / kk2, p = (e % kk2) / k, q = e % k;
+    const int o = ((m * KB + (p >> 4)) * KB + (q >> 4)) * 256 + (p & 15) * 16 + (q & 15);
+    double s = 0.0;
+#pragma unroll
+    for (int ww = 0; ww < GT / 64; ++ww) s += sG[ww][o];
+    out[e] = s;
   }
 }
 
-// loss = (1/B) sum_b (<Guu,Gvv> - 2<Mtu,Mtv> + <Gtu,Gtv>)   (one block)
-__global__ __launch_bounds__(GT) void k_loss_value(const double* grams, int batch, int k, double* loss) {
+// grams[b] = the chunks' sums in chunk order, and b's share of the loss
+__global__ __launch_bounds__(GT) void k_loss_finish(LossArgs a) {
   __shared__ double sh[GT / 64];
-  const int kk2 = k * k;
+  const int b = blockIdx.x, kk2 = a.k * a.k;
   double acc = 0.0;
-  for (int64_t e = threadIdx.x; e < (int64_t)batch * kk2; e += GT) {
-    const int b = (int)(e / kk2), o = (int)(e % kk2);
-    const double* g = grams + (int64_t)b * 6 * kk2;
-    acc += g[0 * kk2 + o] * g[3 * kk2 + o] - 2.0 * g[1 * kk2 + o] * g[4 * kk2 + o] +
-           g[2 * kk2 + o] * g[5 * kk2 + o];
+  for (int e = threadIdx.x; e < kk2; e += GT) {
+    double g[6] = {0., 0., 0., 0., 0., 0.};
+    const double* src = a.gpart + (int64_t)b * (a.cu + a.cv) * 3 * kk2 + e;
+    for (int ch = 0; ch < a.cu; ++ch, src += 3 * kk2)
+#pragma unroll
+      for (int m = 0; m < 3; ++m) g[m] += src[m * kk2];
+    for (int ch = 0; ch < a.cv; ++ch, src += 3 * kk2)
+#pragma unroll
+      for (int m = 0; m < 3; ++m) g[3 + m] += src[m * kk2];
+#pragma unroll
+    for (int m = 0; m < 6; ++m) a.grams[((int64_t)b * 6 + m) * kk2 + e] = g[m];
+    acc += g[0] * g[3] - 2.0 * g[1] * g[4] + g[2] * g[5];
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o, 64);
@@ -227,100 +434,209 @@ __global__ __launch_bounds__(GT) void k_loss_value(const double* grams, int batc
   if (threadIdx.x == 0) {
     double s = 0.0;
     for (int w = 0; w < GT / 64; ++w) s += sh[w];
-    *loss = s / batch;
+    a.lossb[b] = s;
   }
 }
 
-// dy[b][row*k + c]: rows < mu from the U side, the rest from the V side
-__global__ __launch_bounds__(GT) void k_loss_dy(const float* y, const float* TU, const float* TV,
-                                                const double* grams, int batch, int mu, int nv, int k,
-                                                int64_t d_out, float* dy) {
-  const int64_t total = (int64_t)batch * d_out;
-  const int kk2 = k * k;
-  const double sc = 2.0 / batch;
-  for (int64_t e = (int64_t)blockIdx.x * GT + threadIdx.x; e < total; e += (int64_t)gridDim.x * GT) {
-    const int b = (int)(e / d_out);
-    const int64_t o = e % d_out;
-    const bool uside = o < (int64_t)mu * k;
-    const int64_t oo = uside ? o : o - (int64_t)mu * k;
-    const int row = (int)(oo / k), c = (int)(oo % k);
-    const double* g = grams + (int64_t)b * 6 * kk2;
-    const double* Gpp = g + (uside ? 3 : 0) * kk2;  // U side uses Gvv, V side Guu
-    const double* Mt = g + (uside ? 4 : 1) * kk2;   // U side uses Mtv, V side Mtu
-    const float* P = y + (int64_t)b * d_out + (uside ? 0 : (int64_t)mu * k) + (int64_t)row * k;
-    const float* T = (uside ? TU + (int64_t)b * mu * k : TV + (int64_t)b * nv * k) + (int64_t)row * k;
+// dy rows of one batch element, 16 rows a wave at a time: (2 / B) (P G - T M) with G, M in
+// registers (15 us for 64 windows; 55 us with one thread per entry reading G from memory); the first block also forms loss = (1/B) sum_b in a fixed order.  Rows
+// [0, mu) are U's (G = Gvv, M = Mtv), the rest V's (Guu, Mtu).
+template <int KB>
+__global__ __launch_bounds__(GT) void k_loss_dy(LossArgs a) {
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int b = blockIdx.y, k = a.k, kk2 = k * k;
+  if (blockIdx.x == 0 && b == 0 && w == 0) {
     double s = 0.0;
-    for (int j = 0; j < k; ++j) s += (double)P[j] * Gpp[j * k + c] - (double)T[j] * Mt[j * k + c];
-    dy[e] = (float)(sc * s);
+    for (int q = lane; q < a.batch; q += 64) s += a.lossb[q];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (lane == 0) *a.loss = s / a.batch;
+  }
+  const int ub = (a.mu + 15) >> 4, nb = ub + ((a.nv + 15) >> 4);  // 16-row blocks of each side
+  const int stride = gridDim.x * (GT / 64);
+  const double sc = 2.0 / a.batch;
+  const double* g = a.grams + (int64_t)b * 6 * kk2;
+  double G[4 * KB][KB], Mt[4 * KB][KB];  // B operands: K = 4 s + lk, column 16 j + li
+  int side = -1;
+  for (int blk = blockIdx.x * (GT / 64) + w; blk < nb; blk += stride) {
+    const bool us = blk < ub;
+    if ((int)us != side) {
+      side = us;
+      const double* Gp = g + (us ? 3 : 0) * kk2;
+      const double* Mp = g + (us ? 4 : 1) * kk2;
+#pragma unroll
+      for (int s = 0; s < 4 * KB; ++s)
+#pragma unroll
+        for (int j = 0; j < KB; ++j) {
+          const int kr = 4 * s + lk, c = 16 * j + li;
+          const bool ok = kr < k && c < k;
+          G[s][j] = ok ? Gp[kr * k + c] : 0.0;
+          Mt[s][j] = ok ? -Mp[kr * k + c] : 0.0;
+        }
+    }
+    const int rows = us ? a.mu : a.nv, r0 = 16 * (us ? blk : blk - ub);
+    const int64_t off = (int64_t)b * a.d_out + (us ? 0 : (int64_t)a.mu * k);
+    const float* T = us ? a.TU + (int64_t)b * a.mu * k : a.TV + (int64_t)b * a.nv * k;
+    const bool rok = r0 + li < rows;
+    const int64_t ro = (int64_t)(rok ? r0 + li : rows - 1) * k;
+    d4 acc[KB];
+#pragma unroll
+    for (int j = 0; j < KB; ++j) acc[j] = d4{0., 0., 0., 0.};
+#pragma unroll
+    for (int s = 0; s < 4 * KB; ++s) {
+      if (4 * s >= k) break;
+      const int kr = 4 * s + lk;
+      const bool ok = kr < k;
+      const double p = ok ? (double)a.y[off + ro + kr] : 0.0, t = ok ? (double)T[ro + kr] : 0.0;
+#pragma unroll
+      for (int j = 0; j < KB; ++j) {
+        acc[j] = mfma_f64(p, G[s][j], acc[j]);
+        acc[j] = mfma_f64(t, Mt[s][j], acc[j]);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < KB; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = r0 + 4 * r + lk, c = 16 * j + li;
+        if (i < rows && c < k) a.dy[off + (int64_t)i * k + c] = (float)(sc * acc[j][r]);
+      }
   }
 }
 
-__global__ __launch_bounds__(GT) void k_adam(float* p, const float* g, float* m1, float* m2, int64_t n,
-                                             float lr, float b1, float b2, float eps, float bc1,
-                                             float bc2) {
-  for (int64_t i = (int64_t)blockIdx.x * GT + threadIdx.x; i < n; i += (int64_t)gridDim.x * GT) {
-    const float gi = g[i];
-    const float a = fmaf(b1, m1[i], (1.f - b1) * gi);
-    const float v = fmaf(b2, m2[i], (1.f - b2) * gi * gi);
-    m1[i] = a;
-    m2[i] = v;
-    const float mh = a / bc1, vh = v / bc2;
-    p[i] -= lr * mh / (sqrtf(vh) + eps);
+// Adam on all four tensors in one launch (blockIdx.y): 28 bytes a parameter, HBM-bound
+struct AdamArgs {
+  float* p[4];
+  const float* g[4];
+  float* m1[4];
+  float* m2[4];
+  int64_t n[4];
+  float lr, b1, b2, eps, bc1, bc2;
+};
+__global__ __launch_bounds__(GT) void k_adam(AdamArgs a) {
+  const int y = blockIdx.y;
+  float* __restrict__ p = a.p[y];
+  const float* __restrict__ g = a.g[y];
+  float* __restrict__ m1 = a.m1[y];
+  float* __restrict__ m2 = a.m2[y];
+  const int64_t n = a.n[y], n4 = n >> 2;
+  auto one = [&](float gi, float& m, float& v, float& pi) {
+    m = fmaf(a.b1, m, (1.f - a.b1) * gi);
+    v = fmaf(a.b2, v, (1.f - a.b2) * gi * gi);
+    const float mh = m / a.bc1, vh = v / a.bc2;
+    pi -= a.lr * mh / (sqrtf(vh) + a.eps);
+  };
+  const int64_t t0 = (int64_t)blockIdx.x * GT + threadIdx.x, stride = (int64_t)gridDim.x * GT;
+  for (int64_t i = t0; i < n4; i += stride) {
+    const f4 gi = reinterpret_cast<const f4*>(g)[i];
+    f4 m = reinterpret_cast<f4*>(m1)[i], v = reinterpret_cast<f4*>(m2)[i], q = reinterpret_cast<f4*>(p)[i];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float me = m[e], ve = v[e], qe = q[e];
+      one(gi[e], me, ve, qe);
+      m[e] = me;
+      v[e] = ve;
+      q[e] = qe;
+    }
+    reinterpret_cast<f4*>(m1)[i] = m;
+    reinterpret_cast<f4*>(m2)[i] = v;
+    reinterpret_cast<f4*>(p)[i] = q;
   }
+  for (int64_t i = 4 * n4 + t0; i < n; i += stride) one(g[i], m1[i], m2[i], p[i]);
 }
 
 // ---------------------------------------------------------------------------
-// Window statistics.  Thread per pooled block: its pooled value per frame,
-// accumulated over the frames in FP64 for the mean and the (population)
-// standard deviation.  The per-frame means: one block per frame.
-__global__ __launch_bounds__(GT) void k_feat_blocks(const float* X, int64_t W, int64_t H, int frames,
-                                                    int f, const float* shift, const float* scale,
-                                                    float* feat) {
-  const int64_t wl = W / f, hl = H / f, mu = wl * hl, m = W * H;
-  const int64_t p = (int64_t)blockIdx.x * GT + threadIdx.x;
-  if (p >= mu) return;
-  const int64_t by = p / wl, bx = p % wl;
-  const double inv = 1.0 / ((double)f * f);
-  double s1 = 0.0, s2 = 0.0;
-  for (int t = 0; t < frames; ++t) {
-    const float* col = X + (int64_t)t * m + (by * f) * W + bx * f;
-    double v = 0.0;
-    for (int dy = 0; dy < f; ++dy)
-      for (int dx = 0; dx < f; ++dx) v += (double)col[dy * W + dx];
-    v *= inv;
-    s1 += v;
-    s2 += v * v;
+// Window statistics, one launch.  The first `nblk` workgroups take FB pooled blocks each:
+// lane column = pooled block, FG frame groups take every FG-th frame, and the groups'
+// FP64 sums of the pooled value and its square meet in LDS in group order (mean and
+// population standard deviation).  The other workgroups take one frame's mean each.
+// Bound by reading X twice, once from HBM: 10.8 us for 76,800 x 100 (30.7 MB); one thread
+// per pooled block and one 256-thread workgroup per frame took 210 + 76 us.
+// VEC: 4 x 4 pooling read as 16-byte rows (16-byte aligned X), else element loads.
+constexpr int FT = 1024, FB = 32, FG = FT / FB;
+template <bool VEC>
+__global__ __launch_bounds__(FT) void k_features(const float* __restrict__ X, int64_t W, int64_t H, int frames, int f,
+                                                 int64_t nblk, const float* shift, const float* scale, float* feat) {
+  __shared__ double sh[2][FG][FB];
+  const int64_t wl = W / f, mu = wl * (H / f), m = W * H;
+  const int tid = threadIdx.x;
+  if (blockIdx.x < nblk) {
+    const int c = tid % FB, tg = tid / FB;
+    const int64_t p = (int64_t)blockIdx.x * FB + c;
+    double s1 = 0.0, s2 = 0.0;
+    if (p < mu) {
+      const float* base = X + (p / wl * f) * W + p % wl * f;
+      const double inv = 1.0 / ((double)f * f);
+#pragma unroll 2
+      for (int t = tg; t < frames; t += FG) {
+        const float* col = base + (int64_t)t * m;
+        double v = 0.0;
+        if (VEC) {
+          f4 x[4];
+#pragma unroll
+          for (int dy = 0; dy < 4; ++dy) x[dy] = *reinterpret_cast<const f4*>(col + dy * W);
+#pragma unroll
+          for (int dy = 0; dy < 4; ++dy)
+#pragma unroll
+            for (int dx = 0; dx < 4; ++dx) v += (double)x[dy][dx];
+        } else {
+          for (int dy = 0; dy < f; ++dy)
+            for (int dx = 0; dx < f; ++dx) v += (double)col[dy * W + dx];
+        }
+        v *= inv;
+        s1 += v;
+        s2 += v * v;
+      }
+    }
+    sh[0][tg][c] = s1;
+    sh[1][tg][c] = s2;
+    __syncthreads();
+    if (tid < FB && p < mu) {
+      s1 = 0.0;
+      s2 = 0.0;
+      for (int q = 0; q < FG; ++q) {
+        s1 += sh[0][q][c];
+        s2 += sh[1][q][c];
+      }
+      const double mean = s1 / frames;
+      double var = s2 / frames - mean * mean;
+      if (var < 0.0) var = 0.0;
+      float a = (float)mean, b = (float)sqrt(var);
+      if (shift) {
+        a = (a - shift[p]) * scale[p];
+        b = (b - shift[mu + p]) * scale[mu + p];
+      }
+      feat[p] = a;
+      feat[mu + p] = b;
+    }
+    return;
   }
-  const double mean = s1 / frames;
-  double var = s2 / frames - mean * mean;
-  if (var < 0.0) var = 0.0;
-  float a = (float)mean, b = (float)sqrt(var);
-  if (shift) {
-    a = (a - shift[p]) * scale[p];
-    b = (b - shift[mu + p]) * scale[mu + p];
-  }
-  feat[p] = a;
-  feat[mu + p] = b;
-}
-
-__global__ __launch_bounds__(GT) void k_feat_frames(const float* X, int64_t m, int64_t mu2,
-                                                    const float* shift, const float* scale,
-                                                    float* feat) {
-  __shared__ double sh[GT / 64];
-  const int t = blockIdx.x;
-  const float* col = X + (int64_t)t * m;
+  const int64_t t = blockIdx.x - nblk;
+  const float* col = X + t * m;
   double s = 0.0;
-  for (int64_t i = threadIdx.x; i < m; i += GT) s += (double)col[i];
+  int64_t i0 = 0;
+  if (VEC) {  // m is a multiple of 16
+    const f4* c4 = reinterpret_cast<const f4*>(col);
+#pragma unroll 4
+    for (int64_t i = tid; i < m >> 2; i += FT) {
+      const f4 x = c4[i];
+      s += ((double)x[0] + (double)x[1]) + ((double)x[2] + (double)x[3]);
+    }
+    i0 = m;
+  }
+  for (int64_t i = i0 + tid; i < m; i += FT) s += (double)col[i];
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+  double* sw = &sh[0][0][0];
+  if ((tid & 63) == 0) sw[tid >> 6] = s;
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     double r = 0.0;
-    for (int w = 0; w < GT / 64; ++w) r += sh[w];
+    for (int w = 0; w < FT / 64; ++w) r += sw[w];
     float v = (float)(r / m);
-    if (shift) v = (v - shift[mu2 + t]) * scale[mu2 + t];
-    feat[mu2 + t] = v;
+    if (shift) v = (v - shift[2 * mu + t]) * scale[2 * mu + t];
+    feat[2 * mu + t] = v;
   }
 }
 
@@ -387,6 +703,8 @@ struct rpca_mlp {
   float* part;    // split-K partials
   int64_t part_cap;
   double* grams;  // max_batch x 6 x k x k
+  double* gpart;  // row chunks' Gram matrices (loss_chunks)
+  double* lossb;  // max_batch
   int step;
 };
 
@@ -394,32 +712,86 @@ namespace {
 
 // Launch C = op(A) op(B) with the epilogue in `e` (A, B, C, sizes filled by the caller).
 hipError_t gemm(rpca_mlp* net, GemmArgs g, bool ta, bool tb, hipStream_t s) {
-  const int64_t tm = (g.M + BM - 1) / BM, tn = (g.N + BN - 1) / BN;
-  const int64_t tiles = tm * tn;
-  const int64_t kslices = (g.K + BK - 1) / BK;
-  int64_t splits = 1;
-  if (tiles < 512 && kslices >= 8) {
-    splits = (512 + tiles - 1) / tiles;
-    if (splits > kslices / 4) splits = kslices / 4;
-    const int64_t cap = net->part_cap / (g.M * g.N);
+  const int64_t cap = net->part_cap / (g.M * g.N);
+  if (!ta && !tb && g.M <= MV) {
+    // matrix-vector (at most four rows: the predictions of single windows; the tile kernel
+    // pads them to 64 rows and takes 3x as long): 128 (or 32) columns a workgroup, K split until some 512 workgroups are
+    // in flight, at least four values a K group
+    const bool vec = g.N % 4 == 0 && g.ldb % 4 == 0 && ((uintptr_t)g.B & 15) == 0;
+    const int64_t tn = (g.N + MV_L * (vec ? 4 : 1) - 1) / (MV_L * (vec ? 4 : 1));
+    int64_t splits = (512 + tn - 1) / tn;
+    if (splits > g.K / (4 * MV_G)) splits = g.K / (4 * MV_G);
     if (splits > cap) splits = cap;
     if (splits < 1) splits = 1;
+    g.kchunk = (g.K + splits - 1) / splits;
+    splits = (g.K + g.kchunk - 1) / g.kchunk;
+    g.part = splits > 1 ? net->part : nullptr;
+    if (splits > 65535) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)tn, 1, (unsigned)splits);
+    if (vec) hipLaunchKernelGGL((k_gemv<4>), grid, dim3(MV_T), 0, s, g);
+    else hipLaunchKernelGGL((k_gemv<1>), grid, dim3(MV_T), 0, s, g);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || splits == 1) return e;
+    hipLaunchKernelGGL(k_splitk_reduce, dim3(grid_for(g.M * g.N)), dim3(GT), 0, s, g, (int)splits);
+    return hipGetLastError();
   }
-  const int64_t per = (kslices + splits - 1) / splits;
+  const int64_t tm = (g.M + BM - 1) / BM, tn = (g.N + BN - 1) / BN;
+  const int64_t kslices = (g.K + BK - 1) / BK;
+  if (tm > 65535) return hipErrorInvalidValue;
+  if (kslices <= 8) {
+    // short K (a weight gradient over a small batch): one wave per tile
+    g.kchunk = kslices * BK;
+    g.part = nullptr;
+    const dim3 grid((unsigned)((tn + 3) / 4), (unsigned)tm, 1);
+    if (!ta && !tb) hipLaunchKernelGGL((k_gemm<false, false, 1>), grid, dim3(GT), 0, s, g);
+    else if (ta && !tb) hipLaunchKernelGGL((k_gemm<true, false, 1>), grid, dim3(GT), 0, s, g);
+    else if (!ta && tb) hipLaunchKernelGGL((k_gemm<false, true, 1>), grid, dim3(GT), 0, s, g);
+    else hipLaunchKernelGGL((k_gemm<true, true, 1>), grid, dim3(GT), 0, s, g);
+    return hipGetLastError();
+  }
+  // K over the four waves of a workgroup, then over workgroups until two are resident
+  // on every compute unit (the LDS sum holds 64 KB), at least two blocks a wave
+  const int64_t tiles = tm * tn;
+  int64_t splits = tiles < 512 ? 512 / tiles : 1;
+  if (splits > kslices / 8) splits = kslices / 8;
+  if (splits > cap) splits = cap;
+  if (splits < 1) splits = 1;
+  const int64_t per = (kslices + 4 * splits - 1) / (4 * splits);
   g.kchunk = per * BK;
-  splits = (g.K + g.kchunk - 1) / g.kchunk;
+  splits = (g.K + 4 * g.kchunk - 1) / (4 * g.kchunk);
   if (splits < 1) splits = 1;
   g.part = splits > 1 ? net->part : nullptr;
-  if (tm > 65535 || splits > 65535) return hipErrorInvalidValue;
+  if (splits > 65535) return hipErrorInvalidValue;
   const dim3 grid((unsigned)tn, (unsigned)tm, (unsigned)splits);
-  if (!ta && !tb) hipLaunchKernelGGL((k_gemm<false, false>), grid, dim3(GT), 0, s, g);
-  else if (ta && !tb) hipLaunchKernelGGL((k_gemm<true, false>), grid, dim3(GT), 0, s, g);
-  else if (!ta && tb) hipLaunchKernelGGL((k_gemm<false, true>), grid, dim3(GT), 0, s, g);
-  else hipLaunchKernelGGL((k_gemm<true, true>), grid, dim3(GT), 0, s, g);
+  if (!ta && !tb) hipLaunchKernelGGL((k_gemm<false, false, 4>), grid, dim3(GT), 0, s, g);
+  else if (ta && !tb) hipLaunchKernelGGL((k_gemm<true, false, 4>), grid, dim3(GT), 0, s, g);
+  else if (!ta && tb) hipLaunchKernelGGL((k_gemm<false, true, 4>), grid, dim3(GT), 0, s, g);
+  else hipLaunchKernelGGL((k_gemm<true, true, 4>), grid, dim3(GT), 0, s, g);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || splits == 1) return e;
   hipLaunchKernelGGL(k_splitk_reduce, dim3(grid_for(g.M * g.N)), dim3(GT), 0, s, g, (int)splits);
   return hipGetLastError();
+}
+
+// Row chunks of the loss's Gram matrices for a batch: some 1024 workgroups in all, at
+// least 256 rows a chunk; batch (cu + cv) never exceeds loss_chunk_cap(max_batch).
+void loss_chunks(const rpca_mlp* n, int batch, LossArgs* a) {
+  int per = (int)(((int64_t)n->mu * batch + 1023) / 1024);
+  if (per < 256) per = 256;
+  if (per > n->mu) per = n->mu;
+  a->per = per;
+  a->cu = (n->mu + per - 1) / per;
+  a->cv = (n->nv + per - 1) / per;
+}
+int64_t loss_chunk_cap(const rpca_mlp* n) {
+  LossArgs a;
+  int64_t cap = 0;
+  for (int b = 1; b <= n->max_batch; ++b) {
+    loss_chunks(n, b, &a);
+    const int64_t c = (int64_t)b * (a.cu + a.cv);
+    if (c > cap) cap = c;
+  }
+  return cap;
 }
 
 GemmArgs gemm_args(const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc,
@@ -462,6 +834,8 @@ void free_net(rpca_mlp* n) {
   if (n->dz) (void)hipFree(n->dz);
   if (n->part) (void)hipFree(n->part);
   if (n->grams) (void)hipFree(n->grams);
+  if (n->gpart) (void)hipFree(n->gpart);
+  if (n->lossb) (void)hipFree(n->lossb);
   delete n;
 }
 
@@ -502,7 +876,9 @@ int rpca_mlp_create(int32_t d_in, int32_t d_h, int32_t mu, int32_t nv, int32_t k
        hipMalloc(&n->y, (size_t)max_batch * n->d_out * 4) == hipSuccess &&
        hipMalloc(&n->dy, (size_t)max_batch * n->d_out * 4) == hipSuccess &&
        hipMalloc(&n->part, (size_t)n->part_cap * 4) == hipSuccess &&
-       hipMalloc(&n->grams, (size_t)max_batch * 6 * k * k * 8) == hipSuccess;
+       hipMalloc(&n->grams, (size_t)max_batch * 6 * k * k * 8) == hipSuccess &&
+       hipMalloc(&n->gpart, (size_t)loss_chunk_cap(n) * 3 * k * k * 8) == hipSuccess &&
+       hipMalloc(&n->lossb, (size_t)max_batch * 8) == hipSuccess;
   if (!ok) {
     free_net(n);
     return RPCA_ENOMEM;
@@ -550,27 +926,54 @@ int rpca_mlp_loss_grad(rpca_mlp* n, const float* x, const float* TU, const float
   if (!n || !x || !TU || !TV || !loss || batch < 1 || batch > n->max_batch) return RPCA_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   if (forward_into(n, x, batch, n->y, s) != hipSuccess) return RPCA_EHIP;
-  hipLaunchKernelGGL(k_loss_grams, dim3(batch), dim3(GT), 0, s, n->y, TU, TV, n->mu, n->nv, n->k, n->d_out,
-                     n->grams);
-  hipLaunchKernelGGL(k_loss_value, dim3(1), dim3(GT), 0, s, n->grams, batch, n->k, loss);
-  hipLaunchKernelGGL(k_loss_dy, dim3(grid_for((int64_t)batch * n->d_out)), dim3(GT), 0, s, n->y, TU, TV,
-                     n->grams, batch, n->mu, n->nv, n->k, n->d_out, n->dy);
+  LossArgs l;
+  memset(&l, 0, sizeof(l));
+  l.y = n->y;
+  l.TU = TU;
+  l.TV = TV;
+  l.mu = n->mu;
+  l.nv = n->nv;
+  l.k = n->k;
+  l.batch = batch;
+  l.d_out = n->d_out;
+  l.gpart = n->gpart;
+  l.grams = n->grams;
+  l.lossb = n->lossb;
+  l.loss = loss;
+  l.dy = n->dy;
+  loss_chunks(n, batch, &l);
+  const dim3 gg((unsigned)(l.cu + l.cv), (unsigned)batch);
+  const int nb16 = (n->mu + 15) / 16 + (n->nv + 15) / 16;
+  const int dyb = (nb16 + 15) / 16;  // four 16-row blocks a wave
+  const dim3 gd((unsigned)dyb, (unsigned)batch);
+  if (n->k <= 16) hipLaunchKernelGGL((k_loss_grams<1>), gg, dim3(GT), 0, s, l);
+  else hipLaunchKernelGGL((k_loss_grams<2>), gg, dim3(GT), 0, s, l);
+  hipLaunchKernelGGL(k_loss_finish, dim3(batch), dim3(GT), 0, s, l);
+  if (n->k <= 16) hipLaunchKernelGGL((k_loss_dy<1>), gd, dim3(GT), 0, s, l);
+  else hipLaunchKernelGGL((k_loss_dy<2>), gd, dim3(GT), 0, s, l);
   if (hipGetLastError() != hipSuccess) return RPCA_EHIP;
-  // dW2 = h^T dy, db2 = colsum(dy)
+  // dW2 = h^T dy
   GemmArgs a = gemm_args(n->h, n->d_h, n->dy, n->d_out, n->grad[2], n->d_out, n->d_h, n->d_out, batch);
   if (gemm(n, a, true, false, s) != hipSuccess) return RPCA_EHIP;
-  hipLaunchKernelGGL(k_colsum, dim3(grid_for(n->d_out, 1 << 30)), dim3(GT), 0, s, n->dy, (int64_t)batch,
-                     n->d_out, n->grad[3]);
   // dz = (dy W2^T) .* (h > 0)
   GemmArgs b = gemm_args(n->dy, n->d_out, n->param[2], n->d_out, n->dz, n->d_h, batch, n->d_h, n->d_out);
   b.gate = n->h;
   b.ldg = n->d_h;
   if (gemm(n, b, false, true, s) != hipSuccess) return RPCA_EHIP;
-  // dW1 = x^T dz, db1 = colsum(dz)
+  // dW1 = x^T dz
   GemmArgs c = gemm_args(x, n->d_in, n->dz, n->d_h, n->grad[0], n->d_h, n->d_in, n->d_h, batch);
   if (gemm(n, c, true, false, s) != hipSuccess) return RPCA_EHIP;
-  hipLaunchKernelGGL(k_colsum, dim3(grid_for(n->d_h, 1 << 30)), dim3(GT), 0, s, n->dz, (int64_t)batch,
-                     (int64_t)n->d_h, n->grad[1]);
+  // db2 = colsum(dy), db1 = colsum(dz)
+  ColsumArgs cs;
+  cs.A[0] = n->dy;
+  cs.A[1] = n->dz;
+  cs.rows = batch;
+  cs.cols[0] = n->d_out;
+  cs.cols[1] = n->d_h;
+  cs.out[0] = n->grad[3];
+  cs.out[1] = n->grad[1];
+  const int64_t cmax = n->d_out > n->d_h ? n->d_out : n->d_h;
+  hipLaunchKernelGGL(k_colsum, dim3(grid_for(cmax, 1 << 30), 2), dim3(GT), 0, s, cs);
   return hipGetLastError() == hipSuccess ? RPCA_OK : RPCA_EHIP;
 }
 
@@ -581,9 +984,23 @@ int rpca_mlp_adam_step(rpca_mlp* n, float lr, float beta1, float beta2, float ep
   n->step += 1;
   const float bc1 = (float)(1.0 - pow((double)beta1, n->step));
   const float bc2 = (float)(1.0 - pow((double)beta2, n->step));
-  for (int t = 0; t < 4; ++t)
-    hipLaunchKernelGGL(k_adam, dim3(grid_for(n->count[t])), dim3(GT), 0, s, n->param[t], n->grad[t],
-                       n->mom1[t], n->mom2[t], n->count[t], lr, beta1, beta2, eps, bc1, bc2);
+  AdamArgs a;
+  int64_t cmax = 0;
+  for (int t = 0; t < 4; ++t) {
+    a.p[t] = n->param[t];
+    a.g[t] = n->grad[t];
+    a.m1[t] = n->mom1[t];
+    a.m2[t] = n->mom2[t];
+    a.n[t] = n->count[t];
+    if (n->count[t] > cmax) cmax = n->count[t];
+  }
+  a.lr = lr;
+  a.b1 = beta1;
+  a.b2 = beta2;
+  a.eps = eps;
+  a.bc1 = bc1;
+  a.bc2 = bc2;
+  hipLaunchKernelGGL(k_adam, dim3(grid_for((cmax + 3) / 4), 4), dim3(GT), 0, s, a);
   return hipGetLastError() == hipSuccess ? RPCA_OK : RPCA_EHIP;
 }
 
@@ -605,9 +1022,11 @@ int rpca_window_features(const float* X, int64_t W, int64_t H, int32_t frames, i
     return RPCA_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   const int64_t mu = (W / f) * (H / f);
-  hipLaunchKernelGGL(k_feat_blocks, dim3(grid_for(mu, 1 << 30)), dim3(GT), 0, s, X, W, H, frames, f, shift,
-                     scale, feat);
-  hipLaunchKernelGGL(k_feat_frames, dim3(frames), dim3(GT), 0, s, X, W * H, 2 * mu, shift, scale, feat);
+  const int64_t nblk = (mu + FB - 1) / FB;
+  const bool vec = f == 4 && ((uintptr_t)X & 15) == 0;
+  const dim3 grid((unsigned)(nblk + frames));
+  if (vec) hipLaunchKernelGGL((k_features<true>), grid, dim3(FT), 0, s, X, W, H, (int)frames, (int)f, nblk, shift, scale, feat);
+  else hipLaunchKernelGGL((k_features<false>), grid, dim3(FT), 0, s, X, W, H, (int)frames, (int)f, nblk, shift, scale, feat);
   return hipGetLastError() == hipSuccess ? RPCA_OK : RPCA_EHIP;
 }
 
