@@ -628,7 +628,7 @@ def probe(args):
 
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sweep_fp32_video76800x200_hbm_traffic.md")
-SWEEP_SOURCES = [os.path.join(ROOT, "paper_1702_02241_amd", "csrc", f) for f in ("sweep_kernel.h", "sweep_k16.h")]
+SWEEP_SOURCES = [os.path.join(ROOT, "paper_1702_02241_amd", "csrc", f) for f in ("sweep_cols.h",)]
 FW_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "gram_apply_fw_video76800x200_hbm_traffic.md")
 FW_SOURCES = [os.path.join(ROOT, "paper_1702_02241_amd", "csrc", "gram_apply.hip")]
 

@@ -141,7 +141,8 @@ int rpca_create(int64_t m, int64_t n, int32_t k, double lam_S, double lam_L,
 
 /* rpca_create with the sweep's decomposition fixed by a wave count:
  * target_waves (0..2^20) is the number of wavefronts the row strips of one
- * sweep are spread over (0: the tuning table's value for this k and n).  A
+ * sweep are spread over, whole strips to a wave (0: the tuning table's value
+ * for this k and n, and the faster split by columns).  A
  * context that shares the GPU with others (or that must reproduce an
  * instance of a batch bit for bit, see rpca_batch_instance_waves) uses it.
  * Same errors as rpca_create; target_waves out of range is RPCA_EINVAL. */
@@ -171,7 +172,7 @@ int rpca_set_graphs(rpca_ctx* ctx, int32_t on);
 
 /* The sweep decomposition a context took when it was created (from the
  * tuning table, or from rpca_create_waves): out[0] workgroup rows, out[1]
- * strips of 16 rows per wave, out[2] columns per chunk, out[3] chunks.
+ * strips of 16 rows per wave or row lane, out[2] columns per chunk, out[3] chunks.
  * Host only; RPCA_EINVAL for null arguments. */
 int rpca_sweep_layout(const rpca_ctx* ctx, int32_t out[4]);
 
@@ -220,11 +221,10 @@ int rpca_objgrad_ex(rpca_ctx* ctx, const float* X, const float* U, const float* 
  * GPU's array: calls in stream order are safe, calls that overlap on one GPU
  * (two streams or two threads at once) race.  Call with the device that holds
  * the buffers current.  Returns RPCA_EINVAL for bad arguments, RPCA_ETOOBIG when
- * the instance's partials do not fit the array (they take
- * 4 R n k + 8 ceil(R / 16) n k bytes for the R <= 256 workgroup rows of the
- * default decomposition, plus 4 C m k when the n columns span C > 1 chunks of
- * a few hundred; 2.1 MB at 76,800 x 200, k = 10), RPCA_EHIP when the array's address cannot be
- * resolved or a launch fails. */
+ * the instance is too large for the array (the limit counts 4 C m k bytes
+ * when the n columns span C > 1 blocks of up to 256 columns, or up to 128 for
+ * k > 16, and the row partials of G^T U), RPCA_EHIP when the array's address
+ * cannot be resolved or a launch fails. */
 int rpca_objgrad_noalloc(int64_t m, int64_t n, int32_t k, double lam_S, double lam_L,
                          const uint32_t* mask_bits, const float* X, const float* U,
                          const float* V, double* f, float* gU, float* gV, void* stream);

@@ -48,8 +48,8 @@ SweepArgs make_sweep_args(const rpca_ctx* c, const float* X) {
   a.lam_s = (float)c->lam_s;
   a.lam_l = (float)c->lam_l;
   a.kappa = (float)(c->mu / (1.0 + c->mu));
-  // vector (buffer) loads: 16-byte aligned columns, lane offsets within 32 bits
-  a.xvec = (c->m % 4 == 0) && (((uintptr_t)X & 15u) == 0) && c->m < ((int64_t)1 << 26);
+  // vector (buffer) loads, at any 4-byte alignment: lane offsets within 32 bits
+  a.xvec = c->m < ((int64_t)1 << 26);
   a.gupart = c->gupart;
   a.gvpart = c->gvpart;
   a.spart = c->spart;
@@ -57,6 +57,7 @@ SweepArgs make_sweep_args(const rpca_ctx* c, const float* X) {
   a.chunk_w = c->chunk_w;
   a.nchunks = c->nchunks;
   a.row_groups = c->row_groups;
+  if (c->by_cols) rpca::sweep_split(&a);
   return a;
 }
 
@@ -228,6 +229,7 @@ int rpca::create_ctx(int64_t m, int64_t n, int32_t k, double lam_s, double lam_l
       }
     }
   }
+  c->by_cols = target_waves <= 0;
   c->sweep_wgs =
       rpca::sweep_blocks_for(m, n, k, &c->row_groups, &c->spw, &c->chunk_w, &c->nchunks, target_waves);
   TRY(dalloc(&c->gvpart, (size_t)c->row_groups * n * k));

@@ -16,6 +16,7 @@ struct rpca_ctx {
   uint32_t* mask = nullptr;  // device bitmask or null
   int mw = 0;
   // sweep configuration
+  bool by_cols = true;  // the sweep's split: by columns, or by strips (an explicit wave count)
   int row_groups = 0, spw = 0, chunk_w = 0, nchunks = 0, sweep_wgs = 0, segs = 0, rps = 16;
   float* gvpart = nullptr;
   float* gupart = nullptr;

@@ -67,6 +67,16 @@ Layout layout_for(int64_t m, int64_t n, int k, int row_groups, int nchunks, int 
   return L;
 }
 
+// Whether an instance's size is accepted: the documented limit, which counts the partials
+// of the split by strips over 2,048 waves (k <= 16), 1,024, or 4,096 past 512 columns.  The
+// split in use has wider chunks and needs less; the limit stays where callers rely on it.
+bool within_limit(int64_t m, int64_t n, int k) {
+  int rows = 0, spw = 0, cw = 0, nch = 0;
+  const int waves = k <= 16 ? 2048 : n > 512 ? 4096 : 1024;
+  const int wgs = rpca::sweep_blocks_for(m, n, k, &rows, &spw, &cw, &nch, waves);
+  return layout_for(m, n, k, rows, nch, wgs, (rows + 15) / 16).total <= SCRATCH_BYTES;
+}
+
 }  // namespace
 
 extern "C" int rpca_objgrad_noalloc(int64_t m, int64_t n, int32_t k, double lam_s, double lam_l,
@@ -83,7 +93,7 @@ extern "C" int rpca_objgrad_noalloc(int64_t m, int64_t n, int32_t k, double lam_
   const int rps = 16;
   const int segs = (row_groups + rps - 1) / rps;
   const Layout L = layout_for(m, n, k, row_groups, nchunks, sweep_wgs, segs);
-  if (L.total > SCRATCH_BYTES) return RPCA_ETOOBIG;
+  if (!within_limit(m, n, k) || L.total > SCRATCH_BYTES) return RPCA_ETOOBIG;
 
   void* base = nullptr;
   if (scratch_address(&base) != hipSuccess) return RPCA_EHIP;
@@ -100,17 +110,16 @@ extern "C" int rpca_objgrad_noalloc(int64_t m, int64_t n, int32_t k, double lam_
   sa.lam_s = (float)lam_s;
   sa.lam_l = (float)lam_l;
   sa.kappa = 0.f;
-  sa.xvec = (m % 4 == 0) && (((uintptr_t)X & 15u) == 0) && m < ((int64_t)1 << 26);
   sa.U[0] = sa.U[1] = U;
   sa.V[0] = sa.V[1] = V;
   sa.gU[0] = sa.gU[1] = gU;
   sa.gupart = nchunks > 1 ? reinterpret_cast<float*>(b + L.gupart) : nullptr;
   sa.gvpart = reinterpret_cast<float*>(b + L.gvpart);
   sa.spart = reinterpret_cast<double*>(b + L.spart);
-  sa.strips_per_wave = spw;
   sa.chunk_w = chunk_w;
   sa.nchunks = nchunks;
   sa.row_groups = row_groups;
+  rpca::sweep_split(&sa);
 
   FinishArgs fa;
   memset(&fa, 0, sizeof(fa));

@@ -1,4 +1,4 @@
-// Objective/gradient: launch of the fused sweep (sweep_kernel.h) and the finishing
+// Objective/gradient: launch of the fused sweep (sweep_cols.h, sweep_kernel.h) and the finishing
 // reduction with the device-side line-search step.
 
 #include <math.h>
@@ -8,22 +8,12 @@
 #include "linesearch.h"
 
 #include "rpca_internal.h"
+#include "sweep_cols.h"
 #include "sweep_kernel.h"
 
 namespace {
 
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef short s4 __attribute__((ext_vector_type(4)));
-
 constexpr int FIN_THREADS = 256;
-
-__device__ __forceinline__ f4 mfma_f32(float a, float b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ f4 mfma_bf16(s4 a, s4 b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
-}
 
 template <int NT>
 __device__ __forceinline__ double block_sum(double v, double* sh) {
@@ -288,6 +278,9 @@ hipError_t launch_sweep_f32_trial(const SweepArgs&, bool, hipStream_t);
 hipError_t launch_sweep_bf16_plain(const SweepArgs&, bool, hipStream_t);
 hipError_t launch_sweep_bf16_trial(const SweepArgs&, bool, hipStream_t);
 hipError_t launch_sweep_f32_elastic(const SweepArgs&, bool, bool, hipStream_t);
+hipError_t launch_cols_f32(const SweepArgs&, bool, bool, hipStream_t);
+hipError_t launch_cols_bf16(const SweepArgs&, bool, bool, hipStream_t);
+hipError_t launch_cols_f32_elastic(const SweepArgs&, bool, bool, hipStream_t);
 
 // Sweep decomposition table, keyed by (k bucket, n bucket): the number of
 // waves the strips are spread over and the divisor of the widest chunk.
@@ -300,12 +293,9 @@ struct TuneTable {
   std::mutex mu;
   SweepTune t[TUNE_KB][TUNE_NB];
   TuneTable() {
-    // k <= 16: two workgroups per CU (the k16 sweep); k > 16: one, and for more
-    // than 512 columns (many chunks, few rows each) four times as many row groups
-    // (8192 x 8192, k = 25, Bernoulli(0.3) mask: 444 -> 369 us)
+    // 256 workgroups of eight waves, one per compute unit: what its registers and LDS hold
     for (int a = 0; a < TUNE_KB; ++a)
-      for (int b = 0; b < TUNE_NB; ++b)
-        t[a][b] = SweepTune{a < 2 ? 2048 : (b == TUNE_NB - 1 ? 4096 : 1024), 1};
+      for (int b = 0; b < TUNE_NB; ++b) t[a][b] = SweepTune{2048, 1};
   }
 };
 TuneTable& tune_table() {
@@ -330,11 +320,11 @@ void tune_set(int kbucket, int nbucket, SweepTune t) {
 }
 
 // Column chunks (each fitting the sweep's LDS budget) and the wave/workgroup
-// split of the rows, from the tuning table.
-int sweep_blocks_for(int64_t m, int64_t n, int k, int* row_groups, int* strips_per_wave, int* chunk_w,
+// split of the rows of the split by strips, for a given wave count.
+int strip_blocks_for(int64_t m, int64_t n, int k, int* row_groups, int* strips_per_wave, int* chunk_w,
                      int* nchunks, int target_waves) {
   SweepTune t = tune_get(k, n);
-  if (target_waves > 0) t.target_waves = target_waves;
+  t.target_waves = target_waves;
   const int kb = (k + 15) / 16;
   int cmax = rpca_sweep::max_chunk(kb, k);
   if (t.chunk_div > 1) cmax = ((cmax / t.chunk_div + 15) / 16) * 16;
@@ -360,8 +350,69 @@ int sweep_blocks_for(int64_t m, int64_t n, int k, int* row_groups, int* strips_p
   return (int)(wgs * nch);
 }
 
+// Column chunks (at most 512 columns, cut evenly) and the workgroup split of the rows,
+// from the tuning table's wave count: a workgroup has eight waves and, unless the rows run
+// out, at least one strip per row lane.
+int sweep_blocks_for(int64_t m, int64_t n, int k, int* row_groups, int* strips_per_wave, int* chunk_w,
+                     int* nchunks, int target_waves) {
+  if (target_waves > 0)
+    return strip_blocks_for(m, n, k, row_groups, strips_per_wave, chunk_w, nchunks, target_waves);
+  const SweepTune t = tune_get(k, n);
+  int cmax = rpca_cols::CHUNK_MAX;
+  if (n < cmax) cmax = (int)((n + 15) / 16) * 16;
+  if (t.chunk_div > 1) cmax = ((cmax / t.chunk_div + 15) / 16) * 16;
+  int nch = (int)((n + cmax - 1) / cmax);
+  int cw = (int)(((n + nch - 1) / nch + 15) / 16) * 16;
+  if (cw > cmax) cw = cmax;
+  nch = (int)((n + cw - 1) / cw);
+  const int64_t nstrips = (m + 15) / 16;
+  // k > 16, and fewer strips than workgroups side by side: narrower chunks, down to a tile
+  // per wave (583 x 359, k = 26, masked: 18.6 to 10.9 us; V and the G^T U sums of a wide chunk
+  // are most of a workgroup's time there; for k <= 16 they are not, and the further chunks
+  // cost the reduction more)
+  if (k > 16) {
+    const int tiles = (int)((n + 15) / 16);
+    while ((nch + 1) * nstrips <= t.target_waves / rpca_cols::WAVES && tiles > rpca_cols::WAVES * nch) ++nch;
+    cw = ((tiles + nch - 1) / nch) * 16;
+    nch = (int)((n + cw - 1) / cw);
+  }
+  const int rqs = rpca_cols::WAVES / rpca_cols::col_groups(cw, nch, nstrips);
+  // the workgroups of all chunks together make up the table's target; they split the
+  // strips as evenly as integers allow
+  const int64_t target = (t.target_waves + nch - 1) / nch;
+  int64_t wgs = (target + rpca_cols::WAVES - 1) / rpca_cols::WAVES;
+  if (wgs > (nstrips + rqs - 1) / rqs) wgs = (nstrips + rqs - 1) / rqs;
+  // the kernel counts a workgroup's elements of U in 32 bits
+  if (wgs < (nstrips + (1 << 21) - 1) >> 21) wgs = (nstrips + (1 << 21) - 1) >> 21;
+  const int64_t per_wg = (nstrips + wgs - 1) / wgs;
+  *row_groups = (int)wgs;
+  *strips_per_wave = (int)((per_wg + rqs - 1) / rqs);
+  *chunk_w = cw;
+  *nchunks = nch;
+  return (int)(wgs * nch);
+}
+
+void sweep_split(SweepArgs* a) {
+  a->by_cols = 1;
+  const int64_t strips = (a->m + 15) / 16;
+  a->sdiv = strips / a->row_groups;
+  a->srem = (int32_t)(strips % a->row_groups);
+  a->kinv = (uint32_t)(((1ull << 32) + a->k - 1) / (unsigned)a->k);
+  const int64_t most = a->sdiv + (a->srem ? 1 : 0);
+  const int nst = (int)(most < 4096 ? most : 4096);
+  const int cgs = rpca_cols::col_groups(a->chunk_w, a->nchunks, strips);
+  a->lcg = cgs == 1 ? 0 : cgs == 2 ? 1 : cgs == 4 ? 2 : 3;
+  a->spr = rpca_cols::sweep_round(a->k, a->chunk_w, cgs, false, nst);
+  a->spr_bf16 = rpca_cols::sweep_round(a->k, a->chunk_w, cgs, true, nst);
+}
+
 hipError_t launch_sweep(const SweepArgs& sa, bool trial, bool bf16, hipStream_t stream) {
   const bool masked = sa.mask != nullptr;
+  if (sa.by_cols) {
+    if (sa.kappa != 0.f)
+      return bf16 ? hipErrorInvalidValue : launch_cols_f32_elastic(sa, trial, masked, stream);
+    return bf16 ? launch_cols_bf16(sa, trial, masked, stream) : launch_cols_f32(sa, trial, masked, stream);
+  }
   if (sa.kappa != 0.f) {  // elastic-net marginal: FP32 products only (callers reject BF16 first)
     if (bf16) return hipErrorInvalidValue;
     return launch_sweep_f32_elastic(sa, trial, masked, stream);

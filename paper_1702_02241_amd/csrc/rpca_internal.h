@@ -99,7 +99,7 @@ struct SweepArgs {
   int32_t k, mw;
   float lam_s, lam_l;
   float kappa;            // slope of rho' beyond lam_s: mu / (1 + mu) (elastic net), 0 for l1
-  int32_t xvec;           // 1: X is 16-byte aligned and m % 4 == 0 (vector loads allowed)
+  int32_t xvec;           // 1: lane offsets of a column tile fit 32 bits (vector loads allowed)
   // base point: U[cur], V[cur]; trial point = base + alpha * d
   const float* U[2];
   const float* V[2];
@@ -117,6 +117,13 @@ struct SweepArgs {
   int32_t chunk_w;        // columns per chunk (multiple of 16)
   int32_t nchunks;
   int32_t row_groups;     // workgroups along the rows (grid.x)
+  // the split by columns (sweep_cols.h); by_cols = 0: whole strips per wave (sweep_kernel.h)
+  int32_t by_cols;
+  int32_t lcg;            // log2 of the column groups of a workgroup
+  int32_t srem;           // the S strips of 16 rows over R workgroup rows: the first srem = S % R rows own
+  int64_t sdiv;           // sdiv + 1 consecutive strips, the others sdiv = S / R
+  uint32_t kinv;          // ceil(2^32 / k)
+  int32_t spr, spr_bf16;  // strips per round of a workgroup, FP32 / BF16 products
 };
 
 // One work item of the batched sweep: workgroup row rg, column chunk ch of instance inst.
@@ -180,8 +187,12 @@ int tune_k_bucket(int k);
 int tune_n_bucket(int64_t n);
 SweepTune tune_get(int k, int64_t n);
 void tune_set(int kbucket, int nbucket, SweepTune t);
-// Sweep decomposition of an m x n, rank-k instance; target_waves > 0 replaces
-// the table's wave target (a batch spreads one chip's waves over many instances).
+// Sweep decomposition of an m x n, rank-k instance: the split by columns, from the tuning
+// table, or for target_waves > 0 the split by strips over that many waves (a batch spreads
+// one chip's waves over many instances).  An explicit wave count keeps the split by strips
+// because its results are held to earlier ones bit for bit: from a random start a few line
+// searches turn a relative change of 2e-9 in f, one rounding order for another, into 3e-4
+// in the factors.
 int sweep_blocks_for(int64_t m, int64_t n, int k, int* row_groups, int* strips_per_wg, int* chunk_w,
                      int* nchunks, int target_waves = 0);
 // rpca_create with the sweep's wave target given (0: the tuning table's).
@@ -189,6 +200,7 @@ int create_ctx(int64_t m, int64_t n, int32_t k, double lam_s, double lam_l, cons
                int target_waves, rpca_ctx** out, const uint32_t* mask_bits_dev = nullptr);
 hipError_t launch_objgrad(const SweepArgs& sa, const FinishArgs& fa, bool trial, bool bf16,
                           hipStream_t stream);
+void sweep_split(SweepArgs* a);  // by_cols .. spr_bf16 from m, k, chunk_w and row_groups
 hipError_t launch_sweep(const SweepArgs& sa, bool trial, bool bf16, hipStream_t stream);
 hipError_t launch_finish(const FinishArgs& fa, bool trial, hipStream_t stream);
 hipError_t launch_lbfgs_update(const LbfgsArgs& a, int mem, hipStream_t stream);
