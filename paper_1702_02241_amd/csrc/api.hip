@@ -72,9 +72,6 @@ FinishArgs make_finish_args(const rpca_ctx* c) {
   f.gvpart = c->gvpart;
   f.spart = c->spart;
   f.fpart = c->fpart;
-  f.level2 = c->level2;
-  f.segs = c->segs;
-  f.rows_per_seg = c->rps;
   f.counter = c->counters + 0;
   f.nchunks = c->nchunks;
   f.row_groups = c->row_groups;
@@ -235,10 +232,7 @@ int rpca::create_ctx(int64_t m, int64_t n, int32_t k, double lam_s, double lam_l
   TRY(dalloc(&c->gvpart, (size_t)c->row_groups * n * k));
   if (c->nchunks > 1) TRY(dalloc(&c->gupart, (size_t)c->nchunks * m * k));
   TRY(dalloc(&c->spart, (size_t)c->sweep_wgs * RPCA_NSCAL));
-  TRY(dalloc(&c->fpart, (size_t)rpca::finish_blocks(m, n, k, c->nchunks, nullptr) * 3 + 16));
-  c->rps = 16;
-  c->segs = (c->row_groups + c->rps - 1) / c->rps;
-  TRY(dalloc(&c->level2, (size_t)c->segs * n * k));
+  TRY(dalloc(&c->fpart, (size_t)rpca::finish_blocks(m, n, k, c->nchunks, c->row_groups, nullptr) * 4));
   TRY(dalloc(&c->counters, 16));
   if (hipMemset(c->counters, 0, 16 * sizeof(unsigned)) != hipSuccess) {
     rpca_destroy(c);
@@ -348,7 +342,6 @@ void rpca_destroy(rpca_ctx* c) {
   dfree(c->gupart);
   dfree(c->spart);
   dfree(c->fpart);
-  dfree(c->level2);
   dfree(c->counters);
   dfree(c->x[0]);
   dfree(c->x[1]);
@@ -737,10 +730,9 @@ void instance_args(rpca_ctx* c, const float* X, int cur, InstanceArgs* out) {
   sa.pc = c->pc_on ? c->pc_dev : nullptr;
   fa.pc = sa.pc;
   int gvb = 0;
-  out->fin2_blocks = finish_blocks(c->m, c->n, c->k, c->nchunks, &gvb);
+  out->fin_blocks = finish_blocks(c->m, c->n, c->k, c->nchunks, c->row_groups, &gvb);
   out->fa_loop.gv_blocks = gvb;
   out->fa_eval.gv_blocks = gvb;
-  out->fin1_blocks = (int)((c->n * c->k + 255) / 256) * c->segs;  // reduce1: 256 elements per block
   out->lb_blocks = lbfgs_blocks(c->N);
   out->row_groups = c->row_groups;
   out->nchunks = c->nchunks;

@@ -3,7 +3,7 @@
 //   direction  (blocks of all instances in one grid, then one block per instance)
 //   sweep      (one persistent kernel per tile class, each pulling (instance,
 //               row group, chunk) items from its queue; decreasing cost first)
-//   finish     (two batched reductions with the line-search step per instance)
+//   finish     (one batched reduction with the line-search step per instance)
 //   update     (batched history pass, then one block per instance)
 // Per-instance solver states live in device memory and every kernel skips the
 // instances that are not in its phase, so converged instances cost nothing but
@@ -80,11 +80,10 @@ struct rpca_batch {
   };
   std::vector<SweepClass> classes;
   int nitems = 0, lds_max = 0;
-  int tot_fin1 = 0, tot_fin2 = 0, tot_lb = 0;
-  std::vector<int> off_fin1, off_fin2, off_lb;
+  int tot_fin = 0, tot_lb = 0;
+  std::vector<int> off_fin, off_lb;
   SweepItem* d_items = nullptr;
-  int* d_off_fin1 = nullptr;
-  int* d_off_fin2 = nullptr;
+  int* d_off_fin = nullptr;
   int* d_off_lb = nullptr;
   unsigned* d_head = nullptr;
   // argument tables (rewritten by every call: they carry the X pointers)
@@ -123,8 +122,7 @@ void destroy_batch(rpca_batch* b) {
   for (rpca_ctx* c : b->ctx)
     if (c) rpca_destroy(c);
   dfree(b->d_items);
-  dfree(b->d_off_fin1);
-  dfree(b->d_off_fin2);
+  dfree(b->d_off_fin);
   dfree(b->d_off_lb);
   dfree(b->d_head);
   dfree(b->d_sa_loop);
@@ -180,8 +178,8 @@ hipError_t batched_objgrad(rpca_batch* b, bool trial, bool bf16) {
                                                   bf16, s);
     if (e != hipSuccess) return e;
   }
-  return rpca::launch_finish_batch(trial ? b->d_fa_loop : b->d_fa_eval, b->d_off_fin1, b->tot_fin1,
-                                   b->d_off_fin2, b->tot_fin2, b->count, b->d_head, (int)b->classes.size(), trial,
+  return rpca::launch_finish_batch(trial ? b->d_fa_loop : b->d_fa_eval, b->d_off_fin, b->tot_fin, b->count,
+                                   b->d_head, (int)b->classes.size(), trial,
                                    s);
 }
 
@@ -407,8 +405,7 @@ int rpca_batch_create(int32_t count, const int64_t* m, const int64_t* n, const i
   std::vector<rpca::InstanceArgs> ia(count);
   std::vector<SweepItem> items;
   std::vector<double> cost;
-  b->off_fin1.assign(count + 1, 0);
-  b->off_fin2.assign(count + 1, 0);
+  b->off_fin.assign(count + 1, 0);
   b->off_lb.assign(count + 1, 0);
   for (int i = 0; i < count; ++i) {
     rpca::instance_args(b->ctx[i], nullptr, 0, &ia[i]);
@@ -424,8 +421,7 @@ int rpca_batch_create(int32_t count, const int64_t* m, const int64_t* n, const i
         const int64_t cols = std::min<int64_t>(ia[i].chunk_w, n[i] - c0);
         cost.push_back((double)std::max<int64_t>(s1 - s0, 0) * (double)cols * (1.0 + 0.6 * (kb - 1)));
       }
-    b->off_fin1[i + 1] = b->off_fin1[i] + ia[i].fin1_blocks;
-    b->off_fin2[i + 1] = b->off_fin2[i] + ia[i].fin2_blocks;
+    b->off_fin[i + 1] = b->off_fin[i] + ia[i].fin_blocks;
     b->off_lb[i + 1] = b->off_lb[i] + ia[i].lb_blocks;
   }
   // group by tile class, then decreasing cost within a class
@@ -448,13 +444,12 @@ int rpca_batch_create(int32_t count, const int64_t* m, const int64_t* n, const i
     cl.lds = std::max(cl.lds, rpca::sweep_lds_floats(sorted[j].kb, k[i], cwp));
   }
   b->nitems = (int)sorted.size();
-  b->tot_fin1 = b->off_fin1[count];
-  b->tot_fin2 = b->off_fin2[count];
+  b->tot_fin = b->off_fin[count];
   b->tot_lb = b->off_lb[count];
   std::vector<SolverState*> states(count);
   for (int i = 0; i < count; ++i) states[i] = ia[i].state_dev;
-  bool ok = dalloc(&b->d_items, sorted.size()) && dalloc(&b->d_off_fin1, count + 1) &&
-            dalloc(&b->d_off_fin2, count + 1) && dalloc(&b->d_off_lb, count + 1) && dalloc(&b->d_head, b->classes.size()) &&
+  bool ok = dalloc(&b->d_items, sorted.size()) && dalloc(&b->d_off_fin, count + 1) &&
+            dalloc(&b->d_off_lb, count + 1) && dalloc(&b->d_head, b->classes.size()) &&
             dalloc(&b->d_sa_loop, count) && dalloc(&b->d_sa_eval, count) && dalloc(&b->d_fa_loop, count) &&
             dalloc(&b->d_fa_eval, count) && dalloc(&b->d_lu, count) && dalloc(&b->d_ld, count) &&
             dalloc(&b->d_states, count) && dalloc(&b->d_phase, count) &&
@@ -465,9 +460,7 @@ int rpca_batch_create(int32_t count, const int64_t* m, const int64_t* n, const i
   }
   ok = hipMemcpy(b->d_items, sorted.data(), sorted.size() * sizeof(SweepItem), hipMemcpyHostToDevice) ==
            hipSuccess &&
-       hipMemcpy(b->d_off_fin1, b->off_fin1.data(), (count + 1) * sizeof(int), hipMemcpyHostToDevice) ==
-           hipSuccess &&
-       hipMemcpy(b->d_off_fin2, b->off_fin2.data(), (count + 1) * sizeof(int), hipMemcpyHostToDevice) ==
+       hipMemcpy(b->d_off_fin, b->off_fin.data(), (count + 1) * sizeof(int), hipMemcpyHostToDevice) ==
            hipSuccess &&
        hipMemcpy(b->d_off_lb, b->off_lb.data(), (count + 1) * sizeof(int), hipMemcpyHostToDevice) == hipSuccess &&
        hipMemcpy(b->d_states, states.data(), count * sizeof(SolverState*), hipMemcpyHostToDevice) ==

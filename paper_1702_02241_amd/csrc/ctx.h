@@ -17,12 +17,11 @@ struct rpca_ctx {
   int mw = 0;
   // sweep configuration
   bool by_cols = true;  // the sweep's split: by columns, or by strips (an explicit wave count)
-  int row_groups = 0, spw = 0, chunk_w = 0, nchunks = 0, sweep_wgs = 0, segs = 0, rps = 16;
+  int row_groups = 0, spw = 0, chunk_w = 0, nchunks = 0, sweep_wgs = 0;
   float* gvpart = nullptr;
   float* gupart = nullptr;
   double* spart = nullptr;
   double* fpart = nullptr;
-  double* level2 = nullptr;
   unsigned int* counters = nullptr;  // [0] finish, [1] update, [2] direction, [3..] spare
   // solver workspace
   int64_t N = 0;  // (m + n) k padded to a multiple of 256

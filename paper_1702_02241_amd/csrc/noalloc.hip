@@ -9,6 +9,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "rpca_internal.h"
@@ -45,10 +46,10 @@ size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 // Scratch layout of one call (byte offsets; every region 256-byte aligned).
 struct Layout {
-  size_t counters, spart, fpart, level2, gvpart, gupart, total;
+  size_t counters, spart, fpart, gvpart, gupart, total;
 };
 
-Layout layout_for(int64_t m, int64_t n, int k, int row_groups, int nchunks, int sweep_wgs, int segs) {
+Layout layout_for(int64_t m, int64_t n, int k, int row_groups, int nchunks, int sweep_wgs) {
   Layout L;
   size_t o = 0;
   L.counters = o;
@@ -56,9 +57,7 @@ Layout layout_for(int64_t m, int64_t n, int k, int row_groups, int nchunks, int 
   L.spart = o;
   o += align256((size_t)sweep_wgs * RPCA_NSCAL * sizeof(double));
   L.fpart = o;
-  o += align256(((size_t)rpca::finish_blocks(m, n, k, nchunks, nullptr) * 3 + 16) * sizeof(double));
-  L.level2 = o;
-  o += align256((size_t)segs * n * k * sizeof(double));
+  o += align256((size_t)rpca::finish_blocks(m, n, k, nchunks, row_groups, nullptr) * 4 * sizeof(double));
   L.gvpart = o;
   o += align256((size_t)row_groups * n * k * sizeof(float));
   L.gupart = o;
@@ -68,13 +67,20 @@ Layout layout_for(int64_t m, int64_t n, int k, int row_groups, int nchunks, int 
 }
 
 // Whether an instance's size is accepted: the documented limit, which counts the partials
-// of the split by strips over 2,048 waves (k <= 16), 1,024, or 4,096 past 512 columns.  The
+// of the split by strips over 2,048 waves (k <= 16), 1,024, or 4,096 past 512 columns, sums of
+// 16 of them in 64 bits, and the scalars of their reduction in blocks of 256 threads.  The
 // split in use has wider chunks and needs less; the limit stays where callers rely on it.
 bool within_limit(int64_t m, int64_t n, int k) {
   int rows = 0, spw = 0, cw = 0, nch = 0;
   const int waves = k <= 16 ? 2048 : n > 512 ? 4096 : 1024;
   const int wgs = rpca::sweep_blocks_for(m, n, k, &rows, &spw, &cw, &nch, waves);
-  return layout_for(m, n, k, rows, nch, wgs, (rows + 15) / 16).total <= SCRATCH_BYTES;
+  const int64_t vrows = 256 / k, ublocks = nch > 1 ? std::min<int64_t>((m * k + 255) / 256, 4096) : 0;
+  const size_t blocks = (size_t)((n + vrows - 1) / vrows + ublocks);
+  size_t o = align256(16 * sizeof(unsigned)) + align256((size_t)wgs * RPCA_NSCAL * sizeof(double)) +
+             align256((blocks * 3 + 16) * sizeof(double)) + align256((size_t)((rows + 15) / 16) * n * k * sizeof(double)) +
+             align256((size_t)rows * n * k * sizeof(float));
+  if (nch > 1) o += align256((size_t)nch * m * k * sizeof(float));
+  return o <= SCRATCH_BYTES;
 }
 
 }  // namespace
@@ -90,9 +96,7 @@ extern "C" int rpca_objgrad_noalloc(int64_t m, int64_t n, int32_t k, double lam_
   // the decomposition rpca_create would choose for this instance
   int row_groups = 0, spw = 0, chunk_w = 0, nchunks = 0;
   const int sweep_wgs = rpca::sweep_blocks_for(m, n, k, &row_groups, &spw, &chunk_w, &nchunks, 0);
-  const int rps = 16;
-  const int segs = (row_groups + rps - 1) / rps;
-  const Layout L = layout_for(m, n, k, row_groups, nchunks, sweep_wgs, segs);
+  const Layout L = layout_for(m, n, k, row_groups, nchunks, sweep_wgs);
   if (!within_limit(m, n, k) || L.total > SCRATCH_BYTES) return RPCA_ETOOBIG;
 
   void* base = nullptr;
@@ -120,6 +124,8 @@ extern "C" int rpca_objgrad_noalloc(int64_t m, int64_t n, int32_t k, double lam_
   sa.nchunks = nchunks;
   sa.row_groups = row_groups;
   rpca::sweep_split(&sa);
+  // the array is shared: the sweep zeroes the counter, whatever an earlier call left there
+  sa.arm = reinterpret_cast<unsigned*>(b + L.counters);
 
   FinishArgs fa;
   memset(&fa, 0, sizeof(fa));
@@ -134,14 +140,9 @@ extern "C" int rpca_objgrad_noalloc(int64_t m, int64_t n, int32_t k, double lam_
   fa.gupart = sa.gupart;
   fa.gvpart = sa.gvpart;
   fa.spart = sa.spart;
-  fa.level2 = reinterpret_cast<double*>(b + L.level2);
   fa.fpart = reinterpret_cast<double*>(b + L.fpart);
-  // the finishing reduction's first kernel zeroes this counter before the
-  // second one counts on it
   fa.counter = reinterpret_cast<unsigned*>(b + L.counters);
   fa.f_out = f;
-  fa.segs = segs;
-  fa.rows_per_seg = rps;
   fa.nchunks = nchunks;
   fa.row_groups = row_groups;
   fa.sweep_wgs = sweep_wgs;

@@ -3,6 +3,7 @@
 
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "linesearch.h"
@@ -13,63 +14,46 @@
 
 namespace {
 
-constexpr int FIN_THREADS = 256;
-
-template <int NT>
-__device__ __forceinline__ double block_sum(double v, double* sh) {
-  constexpr int W = NT / 64;
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-  __syncthreads();
-  double r = 0.0;
-  if (threadIdx.x == 0)
-    for (int w = 0; w < W; ++w) r += sh[w];
-  return r;
-}
-
 // ---------------------------------------------------------------------------
-// Finishing reduction, two launches (no grid-wide fence in the wide one):
-//   k_reduce1: grid (ceil(nk/256), segs); thread o of block (bx, by) sums the
-//     G^T U partials of workgroup rows [by*rps, (by+1)*rps) -> level2[by][o].
-//   k_reduce2: blocks < gv_blocks (whole rows of V each): gV = sum_by level2 +
-//     lam_l V_t (fixed order), or its preconditioned form;
-//     further blocks (several chunks only): gU = sum over chunks + lam_l U_t.
-//     Each block publishes three scalar partials; the last block to arrive
-//     (thread-0 fence + counter over a handful of blocks) forms f and g^T d
-//     and, in solver mode, runs one step of the line search.
-__device__ __forceinline__ void reduce1_body(const FinishArgs& a, int bx, int by) {
-  // arm the second kernel's last-block counter (it also returns to zero after
-  // every completed reduction; this covers memory that starts undefined)
-  if (bx == 0 && by == 0 && threadIdx.x == 0) *a.counter = 0u;
-  const int64_t nk = a.n * a.k;
-  const int64_t o = (int64_t)bx * FIN_THREADS + threadIdx.x;
-  if (o >= nk) return;
-  const int r0 = by * a.rows_per_seg;
-  int r1 = r0 + a.rows_per_seg;
-  if (r1 > a.row_groups) r1 = a.row_groups;
-  const float* src = a.gvpart + o;
-  double s = 0.0;
-  int r = r0;
-  // eight loads in flight, summed in row order
-  for (; r + 7 < r1; r += 8) {
-    float x[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = src[(int64_t)(r + e) * nk];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) s += (double)x[e];
-  }
-  for (; r < r1; ++r) s += (double)src[(int64_t)r * nk];
-  a.level2[(int64_t)by * nk + o] = s;
+// Finishing reduction, one launch.  Blocks of 16 waves:
+//   bx < gv_blocks: the G^T U partials of whole rows of V.  A wave sums 16 workgroup rows of
+//     64 / k rows of V (lane = output, all 16 loads in flight), `slices` waves side by side;
+//     the slices meet in LDS and are added in row order:
+//     gV = sum + lam_l V_t, or its preconditioned form.
+//   several chunks only: gU = sum over chunks + lam_l U_t, one output per thread.
+//   last: the sweep's scalar partials.
+// Each block publishes up to four scalars; the last one to arrive forms f and g^T d and, in
+// solver mode, runs one step of the line search.
+//
+// Bound by latency: 2 MB of partials at 76,800 x 200, k = 10, and a chain of a few dependent
+// round trips to memory the eight L2 caches share.  As two launches (sums of 16 rows each,
+// then their sum and the rest, fenced by a write-back of the L2 in every block) it took 4.8
+// and 7.2 us there, 4.9 and 43 us at 8192^2, k = 25; this takes 6.9 and 12.5.  The scalars
+// are written through and read past the L2 (agent scope), so no block writes its cache back.
+constexpr int FIN_WAVES = 16;
+constexpr int FIN_THREADS = 64 * FIN_WAVES;
+constexpr int FIN_ROWS = 16;  // workgroup rows per slice
+
+// Waves that share a V row's partials: enough slices of 16 rows for all workgroup rows, a
+// power of two (the block's other waves take further rows of V).
+__host__ __device__ constexpr int finish_slices(int row_groups) {
+  int s = 1;
+  while (s < FIN_WAVES && s * FIN_ROWS < row_groups) s *= 2;
+  return s;
 }
 
-__global__ __launch_bounds__(FIN_THREADS) void k_reduce1(FinishArgs a) { reduce1_body(a, blockIdx.x, blockIdx.y); }
+__device__ __forceinline__ void put_agent(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double get_agent(const double* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // Block bx of the nblk blocks of one instance.
 template <bool TRIAL>
-__device__ __forceinline__ void reduce2_body(const FinishArgs& a, const int bx, const int nblk) {
-  __shared__ double sh[FIN_THREADS / 64];
+__device__ __forceinline__ void finish_body(const FinishArgs& a, const int bx, const int nblk) {
+  __shared__ double sSum[FIN_WAVES][64];
+  __shared__ double sPart[FIN_WAVES][7];
   __shared__ int s_last;
   int outi = 0;
   SolverState* st = a.st;
@@ -77,62 +61,71 @@ __device__ __forceinline__ void reduce2_body(const FinishArgs& a, const int bx, 
     if (st->phase != PH_TRIAL) return;
     outi = 1 - st->cur;
   }
-  const int64_t nk = a.n * a.k, mk = a.m * a.k;
+  const int k = a.k;
+  const int64_t mk = a.m * k;
   const float lam_l = a.lam_l;
   const float* Vt = a.V[outi];
   const float* Ut = a.U[outi];
-  const int tid = threadIdx.x;
-  double vv = 0.0, gvd = 0.0, gud = 0.0;
-  const int k = a.k;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  double p[4] = {0.0, 0.0, 0.0, 0.0};  // this block's scalars (its type says which)
   if (bx < a.gv_blocks) {
-    // whole rows per block: thread (jr, c) of row j = bx * rpb + jr
-    const int rpb = FIN_THREADS / k;
-    const int jr = tid / k, c = tid % k;
-    const int64_t j = (int64_t)bx * rpb + jr;
-    const bool ok = jr < rpb && j < a.n;
-    const int64_t o = j * k + c;
+    const int slices = finish_slices(a.row_groups), groups = FIN_WAVES / slices;
+    const int sl = w & (slices - 1), grp = w / slices;
+    const int rpw = 64 / k, jr = lane / k, c = lane - jr * k;
+    const int64_t j = ((int64_t)bx * groups + grp) * rpw + jr, nk = a.n * k, o = j * k + c;
+    const bool ok = jr < rpw && j < a.n;
+    float v = 0.f, dv = 0.f;
+    if (ok && sl == 0) {
+      v = Vt[o];
+      if (TRIAL) dv = a.dV[o];
+    }
     double s = 0.0;
-    if (ok) {
-      int q = 0;
-      for (; q + 7 < a.segs; q += 8) {  // eight loads in flight, summed in segment order
-        double x[8];
+    for (int r0 = 0; r0 < a.row_groups; r0 += slices * FIN_ROWS) {
+      const int rb = r0 + sl * FIN_ROWS, left = a.row_groups - rb;
+      double t = 0.0;
+      if (ok && left > 0) {
+        const float* src = a.gvpart + (int64_t)rb * nk + o;
+        float x[FIN_ROWS];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = a.level2[(int64_t)(q + e) * nk + o];
+        for (int e = 0; e < FIN_ROWS; ++e) x[e] = src[(e < left ? e : 0) * nk];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) s += x[e];
+        for (int e = 0; e < FIN_ROWS; ++e) t += e < left ? (double)x[e] : 0.0;
       }
-      for (; q < a.segs; ++q) s += a.level2[(int64_t)q * nk + o];
+      if (r0) __syncthreads();  // the slices of the pass before have been read
+      sSum[w][lane] = t;
+      __syncthreads();
+      if (sl == 0)
+        for (int q = 0; q < slices; ++q) s += sSum[w + q][lane];
     }
     if (!a.pc) {
-      if (ok) {
-        const float v = Vt[o];
+      if (ok && sl == 0) {
         const float gvv = (float)(s + (double)lam_l * (double)v);
         a.gV[outi][o] = gvv;
-        vv = (double)v * (double)v;
-        if (TRIAL) gvd = (double)gvv * (double)a.dV[o];
+        p[0] = (double)v * (double)v;
+        if (TRIAL) p[1] = (double)gvv * (double)dv;
       }
     } else {
       // preconditioned variables: grad_B = (G^T A) W + lam_l B M_V, ||V||^2 = sum B M_V B^T
-      __shared__ double sS[FIN_THREADS];
-      sS[tid] = s;
       __syncthreads();
-      if (ok) {
+      if (sl == 0) sSum[w][lane] = s;
+      __syncthreads();
+      if (ok && sl == 0) {
         const float* W = a.pc;
         const float* MV = a.pc + 2 * k * k;
         double t1 = 0.0, t2 = 0.0;
         for (int t = 0; t < k; ++t) {
-          t1 += sS[jr * k + t] * (double)W[t * k + c];
+          t1 += sSum[w][jr * k + t] * (double)W[t * k + c];
           t2 += (double)Vt[j * k + t] * (double)MV[t * k + c];
         }
         const float gvv = (float)(t1 + (double)lam_l * t2);
         a.gV[outi][o] = gvv;
-        vv = (double)Vt[o] * t2;
-        if (TRIAL) gvd = (double)gvv * (double)a.dV[o];
+        p[0] = (double)v * t2;
+        if (TRIAL) p[1] = (double)gvv * (double)dv;
       }
     }
-  } else {
+  } else if (bx < nblk - 1) {
     const float* MU = a.pc ? a.pc + k * k : nullptr;
-    const int64_t stride = (int64_t)(nblk - a.gv_blocks) * FIN_THREADS;
+    const int64_t stride = (int64_t)(nblk - 1 - a.gv_blocks) * FIN_THREADS;
     for (int64_t o = (int64_t)(bx - a.gv_blocks) * FIN_THREADS + tid; o < mk; o += stride) {
       double s = 0.0;
       int cc = 0;
@@ -153,61 +146,61 @@ __device__ __forceinline__ void reduce2_body(const FinishArgs& a, const int bx, 
       }
       const float gu = (float)(s + (double)lam_l * reg);
       a.gU[outi][o] = gu;
-      if (TRIAL) gud += (double)gu * (double)a.dU[o];
+      if (TRIAL) p[0] += (double)gu * (double)a.dU[o];
     }
+    if (!TRIAL) return;  // nothing to publish
+  } else {
+    for (int q = tid; q < a.sweep_wgs; q += FIN_THREADS)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) p[e] += a.spart[(int64_t)q * RPCA_NSCAL + e];
   }
-  const double b0 = block_sum<FIN_THREADS>(vv, sh);
-  const double b1 = block_sum<FIN_THREADS>(gvd, sh);
-  const double b2 = block_sum<FIN_THREADS>(gud, sh);
-  if (tid == 0) {
-    a.fpart[bx * 3 + 0] = b0;
-    a.fpart[bx * 3 + 1] = b1;
-    a.fpart[bx * 3 + 2] = b2;
-    __threadfence();
-    const unsigned prev = atomicAdd(a.counter, 1u);
-    s_last = (prev == (unsigned)nblk - 1u);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    p[e] = rpca_cols::wave_sum63(p[e]);
+    if (lane == 63) sPart[w][e] = p[e];
+  }
+  __syncthreads();
+  if (w == 0) {
+    if (lane < 4) {
+      double t = 0.0;
+#pragma unroll
+      for (int q = 0; q < FIN_WAVES; ++q) t += sPart[q][lane];
+      put_agent(a.fpart + (int64_t)bx * 4 + lane, t);
+    }
+    // the stores have reached the memory the XCDs share before this block counts as arrived
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (lane == 0) {
+      const unsigned arrivals = (unsigned)(TRIAL ? nblk : a.gv_blocks + 1);
+      s_last = __hip_atomic_fetch_add(a.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == arrivals - 1u;
+    }
   }
   __syncthreads();
   if (!s_last) return;
-  __threadfence();
-  double fd = 0.0, uu = 0.0, gd1 = 0.0, g2 = 0.0, p0 = 0.0, p1 = 0.0, p2 = 0.0;
-  for (int q = tid; q < a.sweep_wgs; q += FIN_THREADS) {
-    fd += a.spart[(int64_t)q * RPCA_NSCAL + 0];
-    uu += a.spart[(int64_t)q * RPCA_NSCAL + 1];
-    gd1 += a.spart[(int64_t)q * RPCA_NSCAL + 2];
-    g2 += a.spart[(int64_t)q * RPCA_NSCAL + 3];
-  }
-  for (int b = tid; b < nblk; b += FIN_THREADS) {
-    p0 += a.fpart[b * 3 + 0];
-    p1 += a.fpart[b * 3 + 1];
-    p2 += a.fpart[b * 3 + 2];
-  }
-  {
-    // the seven sums in one pass: wave reductions, then the waves in a fixed order
-    __shared__ double sh7[FIN_THREADS / 64][7];
-    double v[7] = {fd, uu, gd1, g2, p0, p1, p2};
-#pragma unroll
-    for (int e = 0; e < 7; ++e)
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) v[e] += __shfl_xor(v[e], o, 64);
-    if ((tid & 63) == 0)
-#pragma unroll
-      for (int e = 0; e < 7; ++e) sh7[tid >> 6][e] = v[e];
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < 7; ++e) {
-      double r = 0.0;
-      for (int w = 0; w < FIN_THREADS / 64; ++w) r += sh7[w][e];
-      v[e] = r;
+  // ||V||^2, gV . dV and gU . dU over the blocks; the scalar block's four sums
+  double v7[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int b = tid; b < nblk - 1; b += FIN_THREADS) {
+    if (b < a.gv_blocks) {
+      v7[0] += get_agent(a.fpart + (int64_t)b * 4);
+      if (TRIAL) v7[1] += get_agent(a.fpart + (int64_t)b * 4 + 1);
+    } else if (TRIAL) {
+      v7[2] += get_agent(a.fpart + (int64_t)b * 4);
     }
-    fd = v[0];
-    uu = v[1];
-    gd1 = v[2];
-    g2 = v[3];
-    p0 = v[4];
-    p1 = v[5];
-    p2 = v[6];
   }
+  if (tid < 4) v7[3] = get_agent(a.fpart + (int64_t)(nblk - 1) * 4 + tid);
+#pragma unroll
+  for (int e = 0; e < 3; ++e) {
+    v7[e] = rpca_cols::wave_sum63(v7[e]);
+    if (lane == 63) sPart[w][e] = v7[e];
+  }
+  if (tid < 4) sPart[0][3 + tid] = v7[3];
+  __syncthreads();
+  double p0 = 0.0, p1 = 0.0, p2 = 0.0;
+  for (int q = 0; q < FIN_WAVES; ++q) {
+    p0 += sPart[q][0];
+    p1 += sPart[q][1];
+    p2 += sPart[q][2];
+  }
+  const double fd = sPart[0][3], uu = sPart[0][4], gd1 = sPart[0][5], g2 = sPart[0][6];
   if (!TRIAL) {
     if (tid == 0) {
       if (a.f_out) *a.f_out = fd + 0.5 * (double)lam_l * (uu + p0);
@@ -235,38 +228,23 @@ __device__ __forceinline__ void reduce2_body(const FinishArgs& a, const int bx, 
 }
 
 template <bool TRIAL>
-__global__ __launch_bounds__(FIN_THREADS) void k_reduce2(FinishArgs a) {
-  reduce2_body<TRIAL>(a, blockIdx.x, gridDim.x);
+__global__ __launch_bounds__(FIN_THREADS) void k_finish(FinishArgs a) {
+  finish_body<TRIAL>(a, blockIdx.x, gridDim.x);
 }
 
-// ---------------------------------------------------------------------------
-// Batched forms (one launch for every instance of a batch).  off1/off2: block
-// offsets of each instance in the reduce1 / reduce2 grids; reduce1 also
-// re-arms the work queue of the batched sweep that preceded it.
-__device__ __forceinline__ int batch_instance(const int* off, int count, int b) {
+// Batched form (one launch for every instance of a batch).  off: block offsets of each
+// instance in the grid; re-arms the work queues of the batched sweep that preceded it.
+template <bool TRIAL>
+__global__ __launch_bounds__(FIN_THREADS) void k_finish_batch(const FinishArgs* fa, const int* off, int count,
+                                                             unsigned* queue_heads, int nheads) {
+  if (blockIdx.x == 0 && (int)threadIdx.x < nheads) queue_heads[threadIdx.x] = 0u;
   int lo = 0, hi = count;
   while (hi - lo > 1) {
     const int mid = (lo + hi) >> 1;
-    if (off[mid] <= b) lo = mid;
+    if (off[mid] <= (int)blockIdx.x) lo = mid;
     else hi = mid;
   }
-  return lo;
-}
-
-__global__ __launch_bounds__(FIN_THREADS) void k_reduce1_batch(const FinishArgs* fa, const int* off, int count,
-                                                              unsigned* queue_heads, int nheads) {
-  if (blockIdx.x == 0 && (int)threadIdx.x < nheads) queue_heads[threadIdx.x] = 0u;
-  const int i = batch_instance(off, count, blockIdx.x);
-  const FinishArgs& a = fa[i];
-  const int gvb = (int)((a.n * a.k + FIN_THREADS - 1) / FIN_THREADS);
-  const int lb = blockIdx.x - off[i];
-  reduce1_body(a, lb % gvb, lb / gvb);
-}
-
-template <bool TRIAL>
-__global__ __launch_bounds__(FIN_THREADS) void k_reduce2_batch(const FinishArgs* fa, const int* off, int count) {
-  const int i = batch_instance(off, count, blockIdx.x);
-  reduce2_body<TRIAL>(fa[i], blockIdx.x - off[i], off[i + 1] - off[i]);
+  finish_body<TRIAL>(fa[lo], blockIdx.x - off[lo], off[lo + 1] - off[lo]);
 }
 
 }  // namespace
@@ -422,30 +400,25 @@ hipError_t launch_sweep(const SweepArgs& sa, bool trial, bool bf16, hipStream_t 
   return trial ? launch_sweep_f32_trial(sa, masked, stream) : launch_sweep_f32_plain(sa, masked, stream);
 }
 
-int finish_blocks(int64_t m, int64_t n, int k, int nchunks, int* gv_blocks) {
-  const int rpb = FIN_THREADS / k;  // whole rows of V per block
-  const int gvb = (int)((n + rpb - 1) / rpb);
+int finish_blocks(int64_t m, int64_t n, int k, int nchunks, int row_groups, int* gv_blocks) {
+  const int rows = FIN_WAVES / finish_slices(row_groups) * (64 / k);  // whole rows of V per block
+  const int gvb = (int)((n + rows - 1) / rows);
   int gub = 0;
   if (nchunks > 1) {
     // one output per thread (all chunks' partials of it in flight eight at a time)
-    gub = (int)((m * k + FIN_THREADS - 1) / FIN_THREADS);
-    if (gub > 4096) gub = 4096;
+    gub = (int)std::min<int64_t>((m * k + FIN_THREADS - 1) / FIN_THREADS, 1024);
   }
   if (gv_blocks) *gv_blocks = gvb;
-  return gvb + gub;
+  return gvb + gub + 1;
 }
 
 hipError_t launch_finish(const FinishArgs& fa, bool trial, hipStream_t stream) {
   FinishArgs f2 = fa;
-  const int blocks = finish_blocks(fa.m, fa.n, fa.k, fa.nchunks, &f2.gv_blocks);
-  const int gvb = (int)((fa.n * fa.k + FIN_THREADS - 1) / FIN_THREADS);
-  hipLaunchKernelGGL(k_reduce1, dim3(gvb, fa.segs), dim3(FIN_THREADS), 0, stream, f2);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  const int blocks = finish_blocks(fa.m, fa.n, fa.k, fa.nchunks, fa.row_groups, &f2.gv_blocks);
   if (trial)
-    hipLaunchKernelGGL((k_reduce2<true>), dim3(blocks), dim3(FIN_THREADS), 0, stream, f2);
+    hipLaunchKernelGGL((k_finish<true>), dim3(blocks), dim3(FIN_THREADS), 0, stream, f2);
   else
-    hipLaunchKernelGGL((k_reduce2<false>), dim3(blocks), dim3(FIN_THREADS), 0, stream, f2);
+    hipLaunchKernelGGL((k_finish<false>), dim3(blocks), dim3(FIN_THREADS), 0, stream, f2);
   return hipGetLastError();
 }
 
@@ -471,17 +444,15 @@ int sweep_batch_grid(int kb, int tmax, int lds_floats, bool masked, bool trial, 
 int sweep_lds_floats(int kb, int k, int cwp) { return rpca_sweep::lds_floats(kb, k, cwp); }
 int sweep_tmax_class(int kb, int ntiles) { return rpca_sweep::tmax_class(kb, ntiles); }
 
-hipError_t launch_finish_batch(const FinishArgs* fa, const int* off1, int total1, const int* off2, int total2,
-                               int count, unsigned* queue_heads, int nheads, bool trial, hipStream_t stream) {
+hipError_t launch_finish_batch(const FinishArgs* fa, const int* off, int total, int count, unsigned* queue_heads,
+                               int nheads, bool trial, hipStream_t stream) {
   if (nheads > FIN_THREADS) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_reduce1_batch, dim3(total1), dim3(FIN_THREADS), 0, stream, fa, off1, count, queue_heads,
-                     nheads);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   if (trial)
-    hipLaunchKernelGGL((k_reduce2_batch<true>), dim3(total2), dim3(FIN_THREADS), 0, stream, fa, off2, count);
+    hipLaunchKernelGGL((k_finish_batch<true>), dim3(total), dim3(FIN_THREADS), 0, stream, fa, off, count, queue_heads,
+                       nheads);
   else
-    hipLaunchKernelGGL((k_reduce2_batch<false>), dim3(total2), dim3(FIN_THREADS), 0, stream, fa, off2, count);
+    hipLaunchKernelGGL((k_finish_batch<false>), dim3(total), dim3(FIN_THREADS), 0, stream, fa, off, count,
+                       queue_heads, nheads);
   return hipGetLastError();
 }
 

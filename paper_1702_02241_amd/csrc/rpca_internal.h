@@ -124,6 +124,7 @@ struct SweepArgs {
   int64_t sdiv;           // sdiv + 1 consecutive strips, the others sdiv = S / R
   uint32_t kinv;          // ceil(2^32 / k)
   int32_t spr, spr_bf16;  // strips per round of a workgroup, FP32 / BF16 products
+  unsigned int* arm;      // counter of the reduction that follows, set to zero (or null)
 };
 
 // One work item of the batched sweep: workgroup row rg, column chunk ch of instance inst.
@@ -146,13 +147,11 @@ struct FinishArgs {
   const double* spart;
   float* gU[2];
   float* gV[2];
-  double* level2;         // [segs][n*k] first-level sums of the G^T U partials
-  double* fpart;          // [blocks][3] partials of the second reduction
+  double* fpart;          // [blocks][4] scalars of the reduction's blocks
   unsigned int* counter;  // last-block counter (zero between launches)
   double* f_out;          // plain mode: receives f (null: not stored)
   double* aux_out;        // plain mode, optional: phi, ||U||^2, ||V||^2, ||G||_F^2
   int32_t nchunks, row_groups, sweep_wgs;
-  int32_t segs, rows_per_seg;  // workgroup rows are summed in segs segments
   int32_t gv_blocks;      // set by the launcher
   const float* pc;        // preconditioner [W | M_U | M_V] or null (see SweepArgs)
 };
@@ -214,13 +213,13 @@ hipError_t launch_sweep_batch(int kb, int tmax, const SweepArgs* args, const Swe
 int sweep_batch_grid(int kb, int tmax, int lds_floats, bool masked, bool trial, bool bf16);
 int sweep_lds_floats(int kb, int k, int cwp);
 int sweep_tmax_class(int kb, int ntiles);
-hipError_t launch_finish_batch(const FinishArgs* fa, const int* off1, int total1, const int* off2, int total2,
-                               int count, unsigned* queue_heads, int nheads, bool trial, hipStream_t s);
+hipError_t launch_finish_batch(const FinishArgs* fa, const int* off, int total, int count, unsigned* queue_heads,
+                               int nheads, bool trial, hipStream_t s);
 hipError_t launch_lbfgs_update_batch(const LbfgsArgs* la, const int* off, int count, int total_blocks, int mem,
                                     hipStream_t s);
 hipError_t launch_lbfgs_direction_batch(const LbfgsArgs* la, const int* off, int count, int total_blocks,
                                        int mem, hipStream_t s, bool with_final = true);
-int finish_blocks(int64_t m, int64_t n, int k, int nchunks, int* gv_blocks);
+int finish_blocks(int64_t m, int64_t n, int k, int nchunks, int row_groups, int* gv_blocks);
 }  // namespace rpca
 
 // Context internals needed by the certificate / initialisation module.
@@ -277,7 +276,7 @@ struct InstanceArgs {
   SweepArgs sa_loop, sa_eval;
   FinishArgs fa_loop, fa_eval;
   LbfgsArgs lu, ld;
-  int fin1_blocks, fin2_blocks, lb_blocks;
+  int fin_blocks, lb_blocks;
   int row_groups, nchunks, chunk_w, spw;
   bool masked;
   SolverState* state_dev;

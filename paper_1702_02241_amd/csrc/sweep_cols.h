@@ -199,6 +199,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
   constexpr int UB = 16 * 20 + KB * 128;
   static_assert(!(BF16 && ELASTIC), "the elastic net uses FP32 products");
 
+  if (a.arm && rg == 0 && ch == 0 && threadIdx.x == 0) *a.arm = 0u;
   int cur = 0, outi = 0;
   float alpha = 0.f;
   if (TRIAL) {
