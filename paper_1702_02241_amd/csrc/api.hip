@@ -360,6 +360,7 @@ void rpca_destroy(rpca_ctx* c) {
   if (c->gev) (void)hipEventDestroy(c->gev);
   if (c->gstream) (void)hipStreamDestroy(c->gstream);
   rpca::host_free(c->cert_pin);
+  rpca::host_free(c->flags);
   rpca::host_free(c->st_host);
   prof_collect(c);
   for (hipEvent_t e : c->ev_free) (void)hipEventDestroy(e);
@@ -499,6 +500,34 @@ SolverState* ctx_state_host(rpca_ctx* c) { return c->st_host; }
 void host_free(void* p) {
   // a failed free must not stay pending: the next hipGetLastError would report it
   if (p && hipHostFree(p) != hipSuccess) (void)hipGetLastError();
+}
+
+double* ctx_flags(rpca_ctx* c) {
+  if (c->flags) return c->flags;
+  void* p = nullptr;
+  if (hipHostMalloc(&p, 33 * sizeof(double), hipHostMallocCoherent) != hipSuccess) return nullptr;
+  c->flags = static_cast<double*>(p);
+  memset(c->flags, 0, 33 * sizeof(double));
+  c->flags[32] = 1.0;
+  return c->flags;
+}
+
+// Step `want` has written its results when *flag holds its number.  After a
+// millisecond without it (a long step, or one that failed) the stream is waited for,
+// the next step's kernels with it: its result says whether the step ended.
+hipError_t wait_step(const double* flag, double want, hipStream_t s) {
+  const auto t0 = std::chrono::steady_clock::now();
+  for (;;) {
+    for (int i = 0; i < 64; ++i) {
+      double v;
+      __atomic_load(flag, &v, __ATOMIC_ACQUIRE);
+      if (v == want) return hipSuccess;
+#if defined(__x86_64__)
+      __builtin_ia32_pause();
+#endif
+    }
+    if (std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(1)) return hipStreamSynchronize(s);
+  }
 }
 
 void* ctx_pinned(rpca_ctx* c, size_t bytes) {

@@ -1441,7 +1441,7 @@ int certificate_impl(rpca_ctx* c, const float* X, const float* U, const float* V
   const int max_it = 300;
   // The steps on the device (fused pass, a block of at most BLK columns): per step
   // the pass G^T G X, then k_block_ritz (the projection, Rayleigh-Ritz, the stop
-  // test above, the next block, X w_0); the host reads 9 doubles per step.  Unless
+  // test above, the next block, X w_0); which also writes its results to the host.  Unless
   // kernel timing is on, the next step is queued before the host reads this one's
   // stop flag, its kernels doing nothing once the flag is set.  Fills ritz, the
   // next block Xbh and the top Ritz vector.
@@ -1451,17 +1451,12 @@ int certificate_impl(rpca_ctx* c, const float* X, const float* U, const float* V
   const bool dev_ok = ws.pres != nullptr && r <= rpca_ritz::RMAX && n <= rpca_ritz::RT &&
                       o_end <= PIN_SMALL + (size_t)n * 64;
   auto power_dev = [&](std::vector<double>& Xbh, int bb, int* steps) -> int {
-    struct Events {
-      hipEvent_t e[2] = {nullptr, nullptr};
-      ~Events() {
-        for (hipEvent_t x : e)
-          if (x) (void)hipEventDestroy(x);
-      }
-    } ev;
-    for (int i = 0; i < 2; ++i)
-      if (hipEventCreateWithFlags(&ev.e[i], hipEventDisableTiming) != hipSuccess) return RPCA_EHIP;
-    // pinned layout (doubles): [0, 32) two result slots, then the block (n x BL),
+    // pinned layout (doubles): [0, 32) unused, then the block (n x BL),
     // its FP32 copy (n x 16 floats), V_1 and B_n (n x r), V_1^T B_n (r x r)
+    double* const flags = rpca::ctx_flags(c);  // two slots of 16, then the number of the next step
+    if (!flags) return RPCA_ENOMEM;
+    const double seq0 = flags[32];
+    flags[32] += max_it;
     double* blk = pin + o_blk;
     float* w16 = reinterpret_cast<float*>(pin + o_w16);
     for (int64_t i = 0; i < n; ++i)
@@ -1508,11 +1503,10 @@ int certificate_impl(rpca_ctx* c, const float* X, const float* U, const float* V
       ra.conv_rel = 1e-6;
       ra.state = ws.pres + 32;
       ra.vtop = ws.pvtop;
+      ra.host = flags + 16 * (p & 1);
+      ra.seq = seq0 + p;
       hipLaunchKernelGGL(rpca_ritz::k_block_ritz<rpca_ritz::RITZ_CERT>, dim3(1), dim3(rpca_ritz::RT), 0, s, ra);
       if (hipGetLastError() != hipSuccess) return RPCA_EHIP;
-      if (hipMemcpyAsync(pin + 16 * (p & 1), ws.pres, 9 * 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
-          hipEventRecord(ev.e[p & 1], s) != hipSuccess)
-        return RPCA_EHIP;
       return RPCA_OK;
     };
     int rc2 = enqueue(0);
@@ -1520,12 +1514,12 @@ int certificate_impl(rpca_ctx* c, const float* X, const float* U, const float* V
     int p = 0;
     for (;; ++p) {
       if (ahead && p + 1 < max_it && (rc2 = enqueue(p + 1))) return rc2;
-      if (hipEventSynchronize(ev.e[p & 1]) != hipSuccess) return RPCA_EHIP;
-      if (pin[16 * (p & 1)] != 0.0 || p + 1 >= max_it) break;
+      if (rpca::wait_step(flags + 16 * (p & 1) + 1 + BL, seq0 + p, s) != hipSuccess) return RPCA_EHIP;
+      if (flags[16 * (p & 1)] != 0.0 || p + 1 >= max_it) break;
       if (!ahead && (rc2 = enqueue(p + 1))) return rc2;
     }
     *steps = p + 1;
-    const double* slot = pin + 16 * (p & 1);
+    const double* slot = flags + 16 * (p & 1);
     for (int q = 0; q < bb; ++q) ritz[q] = slot[1 + q];
     // the next block (a larger block starts from it) and the top Ritz vector
     if (hipMemcpyAsync(blk, ws.pxd[(p & 1) ^ 1], (size_t)n * BL * 8, hipMemcpyDeviceToHost, s) != hipSuccess)

@@ -46,6 +46,7 @@ struct rpca_ctx {
   size_t cert_ws_bytes = 0;
   void* cert_pin = nullptr;  // pinned host staging of the certificate's small copies
   size_t cert_pin_bytes = 0;
+  double* flags = nullptr;   // pinned, written by kernels: two slots of 16 doubles; [32] the host's count of steps
   // captured groups of solver slots (see run_lbfgs), keyed by what the launches read
   struct SlotGraph {
     const float* X;

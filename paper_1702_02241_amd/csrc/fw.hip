@@ -369,9 +369,8 @@ __global__ __launch_bounds__(FIN_TH) void k_fw_bilinear_finish(const double* __r
 // iteration, eta of the last applied step, phi].  With V = -B u v^T the gap and the
 // exact line search need only these (Alg. 1); done when gap <= tol F or at the
 // last iteration, else st[0..2] take the next t and the update's a, b.
-__global__ void k_fw_step(const double* __restrict__ res, double* __restrict__ st, double lam_l, double tol,
-                          int last) {
-  if (threadIdx.x != 0) return;
+__device__ __forceinline__ void fw_step(const double* __restrict__ res, double* __restrict__ st, double lam_l,
+                                        double tol, int last) {
   const double phi = res[4], gl = res[5], l2 = res[6], t = st[0];
   st[10] = t;
   st[12] = phi;
@@ -409,6 +408,18 @@ __global__ void k_fw_step(const double* __restrict__ res, double* __restrict__ s
   }
 }
 
+// host: the state's copy in pinned host memory, valid once the kernel has ended.
+__global__ void k_fw_step(const double* __restrict__ res, double* __restrict__ st, double lam_l, double tol, int last,
+                          double* __restrict__ host) {
+  __shared__ double s[16];
+  const int i = threadIdx.x;
+  if (i < 16) s[i] = st[i];
+  __syncthreads();
+  if (i == 0) fw_step(res, s, lam_l, tol, last);
+  __syncthreads();
+  if (i < 16) st[i] = host[i] = s[i];
+}
+
 // st = [t, a = 1, b = 0, not done, ...]: the first update pass forms G and the sums.
 __global__ void k_fw_state_init(double* __restrict__ st, double t) {
   const int i = threadIdx.x;
@@ -439,10 +450,10 @@ struct rpca_fw {
   double* part = nullptr;       // block partials
   double* Z = nullptr;          // n x BLK
   double* res = nullptr;        // small device results
-  double* res_host = nullptr;   // pinned copy
+  double* res_host = nullptr;   // pinned, written by the kernels: [8 ..] two slots of a power step's results
   double* st = nullptr;         // 16 doubles: the iteration's step state (k_fw_step)
-  double* st_host = nullptr;    // pinned copy of it
-  hipEvent_t flag_ev[2] = {nullptr, nullptr};  // the power steps' stop-flag copies (two slots)
+  double* st_host = nullptr;    // pinned copy of it, written by the kernel
+  double seq = 1.0;             // number of the next power step
   double* zpin = nullptr;       // pinned staging of the start block (n x BLK doubles)
   float* xpin = nullptr;        // n x (BLK + 16) floats
   // fused G^T G Xb in one pass over G (n <= 256): the blocks as FP32 n x 16 and
@@ -512,8 +523,6 @@ hipError_t fw_timed(rpca_fw* h, int cls, hipStream_t s, Fn&& launch) {
 void fw_free(rpca_fw* h) {
   fw_collect(h);
   for (hipEvent_t e : h->ev_free) (void)hipEventDestroy(e);
-  for (hipEvent_t e : h->flag_ev)
-    if (e) (void)hipEventDestroy(e);
   for (void* p : {(void*)h->mask, (void*)h->G, (void*)h->ypart, (void*)h->Y, (void*)h->y, (void*)h->Xd, (void*)h->Xb,
                   (void*)h->cw, (void*)h->v, (void*)h->part, (void*)h->Z, (void*)h->res, (void*)h->Wf,
                   (void*)h->gpart, (void*)h->st})
@@ -628,8 +637,8 @@ hipError_t fw_left(rpca_fw* h, const float* Xb, hipStream_t s) {
 }
 
 // Linear minimisation: top singular triplet of G by block power iteration with
-// Rayleigh-Ritz, every step on the device (k_block_ritz); the host reads back the
-// stop flag, theta_0 and the residual (24 bytes) per step.  With the fused
+// Rayleigh-Ritz, every step on the device (k_block_ritz), which writes the stop flag,
+// theta_0, the residual and the step's number to pinned host memory.  With the fused
 // pass (and kernel timing off) the next step is queued before the host reads
 // the current one's flag, its kernels doing nothing once the flag is set, so
 // the device does not wait on the host between steps.  On return y = G v
@@ -643,6 +652,8 @@ int fw_lmo(rpca_fw* h, double ptol, double* sigma, int* steps, hipStream_t s, co
   const int64_t ncb = (n + RIGHT_COLS - 1) / RIGHT_COLS;
   const int64_t rblocks = h->rc_right * ncb;
   const int cur0 = h->cur;
+  const double seq0 = h->seq;
+  h->seq += POWER_MAX;
   const bool ahead = h->gpart != nullptr && !h->prof_on;
   // step p: its block is copy cur0 ^ (p & 1), its flag slot p & 1
   auto enqueue_step = [&](int p) -> int {
@@ -694,18 +705,17 @@ int fw_lmo(rpca_fw* h, double ptol, double* sigma, int* steps, hipStream_t s, co
     ra.last = p + 1 == POWER_MAX ? 1 : 0;
     ra.v32 = h->v;
     ra.cw = h->cw;
+    ra.host = h->res_host + 8 + 4 * (p & 1);
+    ra.seq = seq0 + p;
     hipLaunchKernelGGL(rpca_ritz::k_block_ritz<rpca_ritz::RITZ_FW>, dim3(1), dim3(rpca_ritz::RT), 0, s, ra);
     FWCHK(hipGetLastError());
-    double* slot = h->res_host + 8 + 4 * (p & 1);
-    FWCHK(hipMemcpyAsync(slot, h->res + 8, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
-    FWCHK(hipEventRecord(h->flag_ev[p & 1], s));
     return RPCA_OK;
   };
   int rc = enqueue_step(0);
   if (rc) return rc;
   for (int p = 0;; ++p) {
     if (ahead && p + 1 < POWER_MAX && (rc = enqueue_step(p + 1))) return rc;
-    FWCHK(hipEventSynchronize(h->flag_ev[p & 1]));
+    FWCHK(rpca::wait_step(h->res_host + 8 + 4 * (p & 1) + 3, seq0 + p, s));
     // the previous iteration's step state (copied ahead of this minimisation) says done
     if (stop_when && *stop_when != 0.0) return LMO_STOPPED;
     const double* slot = h->res_host + 8 + 4 * (p & 1);
@@ -792,13 +802,13 @@ int rpca_fw_create(int64_t m, int64_t n, double lam_s, double lam_l, const uint8
        hipMalloc(&h->Xb, (size_t)(2 * n * BLK) * 4) == hipSuccess && hipMalloc(&h->cw, BLK * 4) == hipSuccess &&
        hipMalloc(&h->v, (size_t)n * 4) == hipSuccess &&
        hipMalloc(&h->part, (size_t)parts * 8) == hipSuccess && hipMalloc(&h->Z, (size_t)(n * BLK) * 8) == hipSuccess &&
-       hipMalloc(&h->res, 16 * 8) == hipSuccess && hipHostMalloc(&h->res_host, 16 * 8, hipHostMallocDefault) == hipSuccess &&
-       hipMalloc(&h->st, 16 * 8) == hipSuccess && hipHostMalloc(&h->st_host, 16 * 8, hipHostMallocDefault) == hipSuccess &&
+       hipMalloc(&h->res, 16 * 8) == hipSuccess && hipHostMalloc(&h->res_host, 16 * 8, hipHostMallocCoherent) == hipSuccess &&
+       hipMalloc(&h->st, 16 * 8) == hipSuccess && hipHostMalloc(&h->st_host, 16 * 8, hipHostMallocCoherent) == hipSuccess &&
        hipHostMalloc(&h->zpin, (size_t)(n * BLK) * 8, hipHostMallocDefault) == hipSuccess &&
        hipHostMalloc(&h->xpin, (size_t)(n * (BLK + 16)) * 4, hipHostMallocDefault) == hipSuccess;
   if (ok && (hipMemset(h->y, 0, (size_t)m * 4) != hipSuccess || hipMemset(h->v, 0, (size_t)n * 4) != hipSuccess))
     ok = false;
-  for (int e = 0; e < 2 && ok; ++e) ok = hipEventCreateWithFlags(&h->flag_ev[e], hipEventDisableTiming) == hipSuccess;
+  if (ok) memset(h->res_host, 0, 16 * 8);
   if (ok && rpca::gram_apply_fits(n, 0)) {
     // the fused power step: one workgroup per compute unit, two strips a wave at least
     int dev = 0, cus = 0;
@@ -884,8 +894,8 @@ int rpca_fw_solve(rpca_fw* h, const float* X, float* L, double* t_io, int32_t ma
   memset(&fin, 0, sizeof(fin));
   // Per iteration: the minimisation (the host waits on its steps), the bilinear
   // pass, the step (k_fw_step: gap, stop test, eta, the update's a and b) and the
-  // update pass (nothing once done), with no other wait: the step state's copy
-  // is read after the next minimisation's first wait, which ends that
+  // update pass (nothing once done), with no other wait: the step state, which
+  // the step kernel writes to the host, is read after the next minimisation's first wait, which ends that
   // minimisation when the state says done.
   for (int it = 0;; ++it) {
     double sigma = 0.0;
@@ -913,9 +923,8 @@ int rpca_fw_solve(rpca_fw* h, const float* X, float* L, double* t_io, int32_t ma
     if (rc == LMO_STOPPED) break;
     if ((rc = fw_bilinear(h, L, s))) return rc;
     hipLaunchKernelGGL(k_fw_step, dim3(1), dim3(64), 0, s, (const double*)h->res, h->st, lam_l, tol,
-                       it == max_iter ? 1 : 0);
+                       it == max_iter ? 1 : 0, h->st_host);
     FWCHK(hipGetLastError());
-    FWCHK(hipMemcpyAsync(h->st_host, h->st, 16 * sizeof(double), hipMemcpyDeviceToHost, s));
     if ((rc = fw_update(h, X, L, s))) return rc;  // L <- (1 - eta) L + eta V, V = -B u v^T
   }
   *t_io = t;

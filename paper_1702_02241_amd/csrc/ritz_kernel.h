@@ -57,6 +57,12 @@ struct RitzArgs {
   float* Wfn;         // n x 16 FP32 copy of it (columns past BLK zero), or null
   double* res;        // results (see the modes); res[0] is the stop flag
   const double* skip; // null, or res[0] of the previous step
+  // pinned host memory (coherent): the results for the host -- Frank-Wolfe [stop, theta_0,
+  // residual, seq], the certificate [stop, ritz_0 .. ritz_7, seq] -- seq last, so that the
+  // host can poll it instead of waiting on an event between this kernel and the next
+  // (a copy of the results took 4 us a step, the event's packets 5.8)
+  double* host;
+  double seq;         // number of this step
   // Frank-Wolfe: res = [stop, theta_0, residual]
   double ptol;
   int last;           // the last allowed step: stop
@@ -74,6 +80,10 @@ struct RitzArgs {
   double* state;      // BLK: the previous step's Ritz values (read, then rewritten)
   double* vtop;       // n: X w_0 (FP64)
 };
+
+__device__ __forceinline__ void put_host(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 __device__ __forceinline__ double wave_sum(double v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -442,8 +452,14 @@ __device__ __forceinline__ void cert_stop(const RitzArgs& a, const double* sth) 
   if (tid < BLK) {  // after every lane's read of the state (the test above depends on all of them)
     a.state[j] = rj;
     a.res[1 + j] = rj;
+    put_host(a.host + 1 + j, rj);
   }
-  if (tid == 0) a.res[0] = stop ? 1.0 : 0.0;
+  if (tid == 0) {
+    a.res[0] = stop ? 1.0 : 0.0;
+    put_host(a.host, stop ? 1.0 : 0.0);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the wave's stores above
+  if (tid == 0) put_host(a.host + 1 + BLK, a.seq);
 }
 
 template <int MODE>
@@ -678,6 +694,11 @@ __global__ __launch_bounds__(RT) void k_block_ritz(RitzArgs a) {
       res[0] = done ? 1.0 : 0.0;
       res[1] = th0;
       res[2] = resid;
+      put_host(a.host, done ? 1.0 : 0.0);
+      put_host(a.host + 1, th0);
+      put_host(a.host + 2, resid);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      put_host(a.host + 3, a.seq);
     }
     if (tid < BLK) a.cw[tid] = (float)sW[tid * BLK];
   } else if (tid < 64) {

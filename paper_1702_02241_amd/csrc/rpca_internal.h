@@ -263,6 +263,10 @@ int ctx_objgrad_aux(rpca_ctx* c, const float* X, const float* U, const float* V,
 void* ctx_workspace(rpca_ctx* c, size_t bytes, int* fresh);
 // Pinned host staging owned by the context (at least 256 KB, grown on demand;
 // null on failure).  Callers synchronise their copies through it before returning.
+// Pinned: two slots of 16 doubles that kernels write and the host reads, then the host's
+// count of steps; or null.
+double* ctx_flags(rpca_ctx* c);
+hipError_t wait_step(const double* flag, double want, hipStream_t s);
 void* ctx_pinned(rpca_ctx* c, size_t bytes);
 // hipHostFree that leaves no pending error behind when the free fails.
 void host_free(void* p);
