@@ -898,7 +898,6 @@ hipError_t gram_product(const rpca::CtxView& cv, const Workspace& w, const float
   a.part = w.gpart;
   a.skip = skip;
   a.row_groups = w.rg_ga;
-  a.xvec = ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && cv.m % 4 == 0) ? 1 : 0;
   void* tok = nullptr;
   if (cv.ctx && rpca::prof_begin(cv.ctx, s, &tok) != hipSuccess) return hipErrorUnknown;
   hipError_t e = rpca::launch_gram_apply_pass(a, src == SRC_RESID, s);
@@ -1133,12 +1132,12 @@ int get_workspace(rpca_ctx* c, Workspace* w, hipStream_t s) {
   w->rg_right = (int)((nstrips + spr - 1) / spr);
   w->gram_blocks = 256;
   {
-    // fused Gram pass: one workgroup per compute unit, at least two strips per wave
+    // fused Gram pass: two workgroups per compute unit, at least eight strips each
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
       cus = 256;
-    w->rg_ga = (int)std::max<int64_t>(1, std::min<int64_t>(cus, nstrips / 8));
+    w->rg_ga = (int)std::max<int64_t>(1, std::min<int64_t>(2 * cus, nstrips / 8));
   }
   const bool ga = rpca::gram_apply_fits(n, (int)k);
   const size_t sz_Wf = ga ? align_up(n * 16) * 4 : 0;

@@ -669,7 +669,6 @@ int fw_lmo(rpca_fw* h, double ptol, double* sigma, int* steps, hipStream_t s, co
       ga.W = wf_at(h, cur);
       ga.part = h->gpart;
       ga.row_groups = h->rg_ga;
-      ga.xvec = h->vec == 4 ? 1 : 0;
       ga.skip = skip;
       hipError_t ge = hipSuccess;
       FWCHK(fw_timed(h, RPCA_FW_K_RIGHT, s, [&] { ge = rpca::launch_gram_apply_pass(ga, false, s); }));
@@ -810,12 +809,12 @@ int rpca_fw_create(int64_t m, int64_t n, double lam_s, double lam_l, const uint8
     ok = false;
   if (ok) memset(h->res_host, 0, 16 * 8);
   if (ok && rpca::gram_apply_fits(n, 0)) {
-    // the fused power step: one workgroup per compute unit, two strips a wave at least
+    // the fused power step: two workgroups per compute unit, eight strips each at least
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
       cus = 256;
-    h->rg_ga = (int)std::max<int64_t>(1, std::min<int64_t>(cus, ((m + 15) / 16) / 8));
+    h->rg_ga = (int)std::max<int64_t>(1, std::min<int64_t>(2 * cus, ((m + 15) / 16) / 8));
     ok = hipMalloc(&h->Wf, (size_t)(2 * n * 16) * 4) == hipSuccess &&
          hipMalloc(&h->gpart, (size_t)h->rg_ga * n * 16 * 4) == hipSuccess;
   }

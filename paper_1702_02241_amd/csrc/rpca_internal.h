@@ -325,11 +325,9 @@ struct GramApplyArgs {
   const float* W;         // n x 16 row-major FP32, columns past the block zero
   float* part;            // [row_groups][n * 16] per-workgroup sums
   int32_t row_groups;     // workgroups (grid)
-  int32_t xvec;           // 1: X is 16-byte aligned and m % 4 == 0
   const double* skip;     // null, or a device flag: when nonzero the pass and its sum do nothing
 };
 bool gram_apply_fits(int64_t n, int k);
-size_t gram_apply_lds_bytes(int64_t n);
 // The pass: per-workgroup FP32 sums into a.part.
 hipError_t launch_gram_apply_pass(const GramApplyArgs& a, bool resid, hipStream_t s);
 // The sum over workgroups (FP64, fixed order):
