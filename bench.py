@@ -217,7 +217,8 @@ def run_fw(args):
     # the "right" class is the power step: for n <= 256 the fused G^T (G X_b) pass (one read
     # of G, the 16-column block and the per-workgroup sums), else the G^T Y product
     names = ["update", "left", "right", "bilinear"]
-    alg = [16 * m * n, 4 * m * n + 4 * blk * m, 4 * m * n + (64 * n if n <= 256 else 4 * blk * m),
+    # (and "left" y = G v with the row sums of L v, both matrices read once)
+    alg = [16 * m * n, 8 * m * n + 4 * m if n <= 256 else 4 * m * n + 4 * blk * m, 4 * m * n + (64 * n if n <= 256 else 4 * blk * m),
            4 * m * n + 4 * m]
     per = {nm: dict(launches=int(launches[i]) // max(args.steps, 1), ms=round(ms[i] / max(args.steps, 1), 3),
                     us_per_launch=round(1000 * ms[i] / max(launches[i], 1), 2)) for i, nm in enumerate(names)}

@@ -78,11 +78,12 @@ void rpca_fw_destroy(rpca_fw* fw);
  * and optionally resets the counters.  RPCA_EINVAL on a null handle or out. */
 enum rpca_fw_kernel {
   RPCA_FW_K_UPDATE = 0,    /* L <- a L + b y v^T and G: reads L, X; writes L, G */
-  RPCA_FW_K_LEFT = 1,      /* partial Y = G Xb over column chunks: reads G */
+  RPCA_FW_K_LEFT = 1,      /* n <= 256: y = G v and the row sums of P_Omega(L) v: reads G, L;
+                              else partial Y = G Xb over column chunks: reads G */
   RPCA_FW_K_RIGHT = 2,     /* the power step: for n <= 256 the per-workgroup sums of
                               G^T (G Xb) in one pass over G (reads G), else the
                               partial Z = G^T Y over row chunks (reads G and Y) */
-  RPCA_FW_K_BILINEAR = 3   /* u^T P_Omega(L) v: reads L */
+  RPCA_FW_K_BILINEAR = 3   /* n > 256: u^T P_Omega(L) v: reads L */
 };
 typedef struct rpca_fw_profile {
   int64_t launches[4];

@@ -38,6 +38,7 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 
 constexpr int TH = 256;         // threads per block of the streaming kernels
 constexpr int BLK = 8;          // vectors in the power-iteration block
+constexpr int UPD_ITER = 4;     // row groups per thread in the update pass
 constexpr int LEFT_COLS = 32;   // columns per block of Y = G Xb
 constexpr int RIGHT_COLS = 4;   // columns per block of Z = G^T Y
 constexpr int RIGHT_ITER = 4;   // row groups per thread in Z = G^T Y
@@ -83,8 +84,9 @@ __device__ __forceinline__ unsigned obs_bits(const uint32_t* mask, int mw, int64
 }
 
 // L <- a L + b y_i v_j;  G = P_Omega(clip(L - X));  block partials of
-// phi(L), <G, L>, sum_Omega L^2.  Block b covers rows (b % rb) * TH * VEC ... of
-// column b / rb.
+// phi(L), <G, L>, sum_Omega L^2.  Block b covers rows (b % rb) * TH * VEC * UPD_ITER ... of
+// column b / rb (one row group per thread, 15,000 blocks at 76800 x 200, left the one block
+// that sums their partials 7.5 us; four: 4.7).
 template <int VEC, bool MASK>
 // a = st[1], b = st[2] from the step state; nothing once st[3] (done) is set.
 __global__ __launch_bounds__(TH) void k_fw_update(float* __restrict__ L, const float* __restrict__ X,
@@ -96,10 +98,12 @@ __global__ __launch_bounds__(TH) void k_fw_update(float* __restrict__ L, const f
   const float a = (float)st[1], b = (float)st[2];
   const int64_t blk = blockIdx.x;
   const int64_t j = blk / rb;
-  const int64_t i0 = (blk % rb) * (TH * VEC) + (int64_t)threadIdx.x * VEC;
+  const float bv = b != 0.f ? b * v[j] : 0.f;
   double s[3] = {0.0, 0.0, 0.0};
-  if (i0 < m) {
-    const float bv = b != 0.f ? b * v[j] : 0.f;
+#pragma unroll
+  for (int it = 0; it < UPD_ITER; ++it) {
+    const int64_t i0 = ((blk % rb) * UPD_ITER + it) * (TH * VEC) + (int64_t)threadIdx.x * VEC;
+    if (i0 >= m) break;
     const int64_t off = j * m + i0;
     float l[VEC], x[VEC], yy[VEC];
     if (VEC == 4) {
@@ -298,6 +302,76 @@ __global__ __launch_bounds__(TH) void k_fw_combine(const float* __restrict__ Y, 
   y[i] = s;
 }
 
+// Fused step pass (n <= 256): y = G v and, row by row, z = P_Omega(L) v and q_i = the sum
+// over the row's observed entries of v_j^2, in one pass over G and L; block partials of
+// sum y_i z_i and sum y_i^2 q_i (u^T P_Omega(L) v and sum_Omega u_i^2 v_j^2 times sigma and
+// sigma^2, u = y / sigma).  A block of eight waves takes 64 VEC rows, a wave an eighth of
+// the columns (FP32 chains of n / 8, the waves added in order).  Bound by the two reads: at
+// 76800 x 200 it takes NEWB us; the left product of the whole block with its chunk sums and
+// combination, and the bilinear pass with its finish, took 15.5 + 6.1 + 4.1 and 12.7 + 3.9.
+constexpr int RW = 8;  // waves per block
+template <int VEC, bool MASK>
+__global__ __launch_bounds__(64 * RW) void k_fw_rows(const float* __restrict__ G, const float* __restrict__ L,
+                                                     const float* __restrict__ v, const uint32_t* __restrict__ mask,
+                                                     int mw, int64_t m, int n, float* __restrict__ y,
+                                                     double* __restrict__ part) {
+  __shared__ float sh[3][RW][64 * VEC];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i0 = ((int64_t)blockIdx.x * 64 + lane) * VEC;
+  const bool ok = i0 < m;
+  float ay[VEC], az[VEC], aq[VEC];
+#pragma unroll
+  for (int c = 0; c < VEC; ++c) ay[c] = az[c] = aq[c] = 0.f;
+  if (ok) {
+#pragma unroll 5
+    for (int j = w * n / RW; j < (w + 1) * n / RW; ++j) {
+      const int64_t off = j * m + i0;
+      const float vj = v[j];
+      float g[VEC], l[VEC];
+      if (VEC == 4) {
+        const f4 gv = load4(G + off), lv = load4(L + off);
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) {
+          g[c] = gv[c];
+          l[c] = lv[c];
+        }
+      } else {
+        g[0] = G[off];
+        l[0] = L[off];
+      }
+      const unsigned bits = obs_bits<VEC, MASK>(mask, mw, j, i0);
+#pragma unroll
+      for (int c = 0; c < VEC; ++c) {
+        const bool o = !MASK || ((bits >> c) & 1u);
+        ay[c] = fmaf(g[c], vj, ay[c]);  // G is zero where nothing is observed
+        az[c] = o ? fmaf(l[c], vj, az[c]) : az[c];
+        aq[c] = o ? fmaf(vj, vj, aq[c]) : aq[c];
+      }
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < VEC; ++c) {
+    sh[0][w][c * 64 + lane] = ay[c];
+    sh[1][w][c * 64 + lane] = az[c];
+    sh[2][w][c * 64 + lane] = aq[c];
+  }
+  __syncthreads();
+  double s[2] = {0.0, 0.0};
+  // wave w: rows of component c = w (VEC = 4) or of wave 0 (VEC = 1)
+  if (w < VEC) {
+    float t[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < RW; ++q)
+#pragma unroll
+      for (int e = 0; e < 3; ++e) t[e] += sh[e][q][w * 64 + lane];
+    if (ok) y[i0 + w] = t[0];
+    s[0] = (double)t[0] * (double)t[1];
+    s[1] = (double)t[0] * (double)t[0] * (double)t[2];
+  }
+  block_sums<2, 64 * RW>(s, part + (int64_t)blockIdx.x * 2);
+}
+
 // Bilinear pass over a chunk of rows of column j (observed entries only):
 // part[0] = sum_i A_ij u_i, part[1] = sum_i u_i^2, u_i = ws w_i.
 template <int VEC, bool MASK>
@@ -409,11 +483,27 @@ __device__ __forceinline__ void fw_step(const double* __restrict__ res, double* 
 }
 
 // host: the state's copy in pinned host memory, valid once the kernel has ended.
-__global__ void k_fw_step(const double* __restrict__ res, double* __restrict__ st, double lam_l, double tol, int last,
-                          double* __restrict__ host) {
-  __shared__ double s[16];
+// nrows > 0: the bilinear sums are the fused pass's block partials, times sigma and sigma^2.
+constexpr int STEP_TH = 256;
+__global__ __launch_bounds__(STEP_TH) void k_fw_step(double* __restrict__ res, double* __restrict__ st, double lam_l,
+                                                     double tol, int last, double* __restrict__ host,
+                                                     const double* __restrict__ rows, int64_t nrows) {
+  __shared__ double s[16], p[2];
   const int i = threadIdx.x;
   if (i < 16) s[i] = st[i];
+  if (nrows > 0) {
+    double q[2] = {0.0, 0.0};
+    for (int64_t b = i; b < nrows; b += STEP_TH) {
+      q[0] += rows[2 * b];
+      q[1] += rows[2 * b + 1];
+    }
+    block_sums<2, STEP_TH>(q, p);
+    if (i == 0) {
+      const double sigma = sqrt(fmax(res[9], 0.0));
+      res[2] = p[0] / sigma;  // (not used without a step: sigma <= lam_L)
+      res[3] = p[1] / (sigma * sigma);
+    }
+  }
   __syncthreads();
   if (i == 0) fw_step(res, s, lam_l, tol, last);
   __syncthreads();
@@ -462,7 +552,7 @@ struct rpca_fw {
   float* gpart = nullptr;
   int rg_ga = 0;
   std::vector<double> Xh;       // the start block on the host (FP64)
-  int64_t rb_upd = 0, nchunks_left = 0, rc_right = 0, rc_bil = 0;
+  int64_t rb_upd = 0, rb_rows = 0, nchunks_left = 0, rc_right = 0, rc_bil = 0;
   bool x_valid = false;
   // optional kernel timing (rpca_fw_profile_*): event pairs per kernel class
   bool prof_on = false;
@@ -541,23 +631,24 @@ void fw_free(rpca_fw* h) {
 // L <- a L + b y v^T (a, b from the step state), G and the three sums into
 // res[4..6] (host copy queued).
 int fw_update(rpca_fw* h, const float* X, float* L, hipStream_t s) {
-  const int64_t blocks = h->rb_upd * h->n;
+  const int64_t rb = (h->m + (int64_t)TH * h->vec * UPD_ITER - 1) / ((int64_t)TH * h->vec * UPD_ITER);
+  const int64_t blocks = rb * h->n;
   const float ls = (float)h->lam_s;
   FWCHK(fw_timed(h, RPCA_FW_K_UPDATE, s, [&] {
     if (h->vec == 4) {
       if (h->mask)
         hipLaunchKernelGGL((k_fw_update<4, true>), dim3((unsigned)blocks), dim3(TH), 0, s, L, X, h->mask, h->mw, h->m,
-                           h->rb_upd, (const double*)h->st, h->y, h->v, ls, h->G, h->part);
+                           rb, (const double*)h->st, h->y, h->v, ls, h->G, h->part);
       else
         hipLaunchKernelGGL((k_fw_update<4, false>), dim3((unsigned)blocks), dim3(TH), 0, s, L, X, h->mask, h->mw,
-                           h->m, h->rb_upd, (const double*)h->st, h->y, h->v, ls, h->G, h->part);
+                           h->m, rb, (const double*)h->st, h->y, h->v, ls, h->G, h->part);
     } else {
       if (h->mask)
         hipLaunchKernelGGL((k_fw_update<1, true>), dim3((unsigned)blocks), dim3(TH), 0, s, L, X, h->mask, h->mw, h->m,
-                           h->rb_upd, (const double*)h->st, h->y, h->v, ls, h->G, h->part);
+                           rb, (const double*)h->st, h->y, h->v, ls, h->G, h->part);
       else
         hipLaunchKernelGGL((k_fw_update<1, false>), dim3((unsigned)blocks), dim3(TH), 0, s, L, X, h->mask, h->mw,
-                           h->m, h->rb_upd, (const double*)h->st, h->y, h->v, ls, h->G, h->part);
+                           h->m, rb, (const double*)h->st, h->y, h->v, ls, h->G, h->part);
     }
   }));
   hipLaunchKernelGGL(k_sum_parts<3>, dim3(1), dim3(FIN_TH), 0, s, (const double*)h->part, blocks, h->res + 4);
@@ -722,17 +813,35 @@ int fw_lmo(rpca_fw* h, double ptol, double* sigma, int* steps, hipStream_t s, co
     // the kernel sets the flag at the last allowed step; the host stops there too
     if (slot[0] != 0.0 || p + 1 >= POWER_MAX) {
       const int cur = cur0 ^ (p & 1);
-      // y = G v = (G Xb) w_0 for this step's block
-      if (h->gpart) FWCHK(fw_left(h, xb_at(h, cur), s));
-      hipLaunchKernelGGL(k_fw_combine, dim3((unsigned)((m + TH - 1) / TH)), dim3(TH), 0, s, (const float*)h->Y,
-                         (const float*)h->cw, m, h->y);
-      FWCHK(hipGetLastError());
+      if (!h->gpart) {  // y = G v = (G Xb) w_0 for this step's block
+        hipLaunchKernelGGL(k_fw_combine, dim3((unsigned)((m + TH - 1) / TH)), dim3(TH), 0, s, (const float*)h->Y,
+                           (const float*)h->cw, m, h->y);
+        FWCHK(hipGetLastError());
+      }
       *sigma = sqrt(slot[1]);
       h->cur = cur ^ 1;
       return RPCA_OK;
     }
     if (!ahead && (rc = enqueue_step(p + 1))) return rc;
   }
+}
+
+// y = G v and the row sums of the bilinear pass, over G and L at once
+hipError_t fw_rows(rpca_fw* h, const float* L, hipStream_t s) {
+  const dim3 grid((unsigned)h->rb_rows), block(64 * RW);
+  return fw_timed(h, RPCA_FW_K_LEFT, s, [&] {
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, block, 0, s, (const float*)h->G, L, (const float*)h->v,
+                         (const uint32_t*)h->mask, h->mw, h->m, (int)h->n, h->y, h->part);
+    };
+    if (h->vec == 4) {
+      if (h->mask) go(k_fw_rows<4, true>);
+      else go(k_fw_rows<4, false>);
+    } else {
+      if (h->mask) go(k_fw_rows<1, true>);
+      else go(k_fw_rows<1, false>);
+    }
+  });
 }
 
 // u^T P_Omega(L) v and sum_Omega u_i^2 v_j^2 with u = y / sigma into res[2..3]
@@ -787,7 +896,7 @@ int rpca_fw_create(int64_t m, int64_t n, double lam_s, double lam_l, const uint8
   const int64_t rb1 = (m + TH - 1) / TH;
   const int64_t rcr1 = (m + (int64_t)TH * RIGHT_ITER - 1) / ((int64_t)TH * RIGHT_ITER);
   const int64_t rcb1 = (m + (int64_t)TH * COL_ITER - 1) / ((int64_t)TH * COL_ITER);
-  const int64_t parts = std::max(std::max(rb1 * n * 3, rcr1 * n * BLK), rcb1 * n * 2);
+  const int64_t parts = std::max(std::max(std::max(rb1 * n * 3, rcr1 * n * BLK), rcb1 * n * 2), (m + 63) / 64 * 2);
   bool ok = true;
   try {
     h->Xh.assign((size_t)n * BLK, 0.0);
@@ -875,6 +984,7 @@ int rpca_fw_solve(rpca_fw* h, const float* X, float* L, double* t_io, int32_t ma
   h->vec = (h->m % 4 == 0 && al) ? 4 : 1;
   h->rb_upd = (h->m + TH * h->vec - 1) / (TH * h->vec);
   h->rc_right = (h->m + (int64_t)TH * h->vec * RIGHT_ITER - 1) / ((int64_t)TH * h->vec * RIGHT_ITER);
+  h->rb_rows = (h->m + 64 * h->vec - 1) / (64 * h->vec);
   h->rc_bil = (h->m + (int64_t)TH * h->vec * COL_ITER - 1) / ((int64_t)TH * h->vec * COL_ITER);
   int rc;
   if (!h->x_valid) {
@@ -920,9 +1030,10 @@ int rpca_fw_solve(rpca_fw* h, const float* X, float* L, double* t_io, int32_t ma
       if (st[3] != 0.0) break;
     }
     if (rc == LMO_STOPPED) break;
-    if ((rc = fw_bilinear(h, L, s))) return rc;
-    hipLaunchKernelGGL(k_fw_step, dim3(1), dim3(64), 0, s, (const double*)h->res, h->st, lam_l, tol,
-                       it == max_iter ? 1 : 0, h->st_host);
+    if (h->gpart) FWCHK(fw_rows(h, L, s));
+    else if ((rc = fw_bilinear(h, L, s))) return rc;
+    hipLaunchKernelGGL(k_fw_step, dim3(1), dim3(STEP_TH), 0, s, h->res, h->st, lam_l, tol, it == max_iter ? 1 : 0,
+                       h->st_host, (const double*)h->part, h->gpart ? h->rb_rows : 0);
     FWCHK(hipGetLastError());
     if ((rc = fw_update(h, X, L, s))) return rc;  // L <- (1 - eta) L + eta V, V = -B u v^T
   }
