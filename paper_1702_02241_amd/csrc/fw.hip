@@ -307,7 +307,7 @@ __global__ __launch_bounds__(TH) void k_fw_combine(const float* __restrict__ Y, 
 // sum y_i z_i and sum y_i^2 q_i (u^T P_Omega(L) v and sum_Omega u_i^2 v_j^2 times sigma and
 // sigma^2, u = y / sigma).  A block of eight waves takes 64 VEC rows, a wave an eighth of
 // the columns (FP32 chains of n / 8, the waves added in order).  Bound by the two reads: at
-// 76800 x 200 it takes NEWB us; the left product of the whole block with its chunk sums and
+// 76800 x 200 it takes 20.7 us; the left product of the whole block with its chunk sums and
 // combination, and the bilinear pass with its finish, took 15.5 + 6.1 + 4.1 and 12.7 + 3.9.
 constexpr int RW = 8;  // waves per block
 template <int VEC, bool MASK>

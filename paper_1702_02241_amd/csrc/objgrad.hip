@@ -11,6 +11,7 @@
 #include "rpca_internal.h"
 #include "sweep_cols.h"
 #include "sweep_kernel.h"
+#include "wave_sum.h"
 
 namespace {
 
@@ -42,13 +43,6 @@ __host__ __device__ constexpr int finish_slices(int row_groups) {
   return s;
 }
 
-__device__ __forceinline__ void put_agent(double* p, double v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ double get_agent(const double* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // Block bx of the nblk blocks of one instance.
 template <bool TRIAL>
 __device__ __forceinline__ void finish_body(const FinishArgs& a, const int bx, const int nblk) {
@@ -58,8 +52,10 @@ __device__ __forceinline__ void finish_body(const FinishArgs& a, const int bx, c
   int outi = 0;
   SolverState* st = a.st;
   if (TRIAL) {
-    if (st->phase != PH_TRIAL) return;
-    outi = 1 - st->cur;
+    const int phase = st->phase, cur = st->cur;
+    LOADED(phase, cur);
+    if (phase != PH_TRIAL) return;
+    outi = 1 - cur;
   }
   const int k = a.k;
   const int64_t mk = a.m * k;
@@ -156,7 +152,7 @@ __device__ __forceinline__ void finish_body(const FinishArgs& a, const int bx, c
   }
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    p[e] = rpca_cols::wave_sum63(p[e]);
+    p[e] = wave_sum63(p[e]);
     if (lane == 63) sPart[w][e] = p[e];
   }
   __syncthreads();
@@ -167,12 +163,7 @@ __device__ __forceinline__ void finish_body(const FinishArgs& a, const int bx, c
       for (int q = 0; q < FIN_WAVES; ++q) t += sPart[q][lane];
       put_agent(a.fpart + (int64_t)bx * 4 + lane, t);
     }
-    // the stores have reached the memory the XCDs share before this block counts as arrived
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (lane == 0) {
-      const unsigned arrivals = (unsigned)(TRIAL ? nblk : a.gv_blocks + 1);
-      s_last = __hip_atomic_fetch_add(a.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == arrivals - 1u;
-    }
+    if (lane == 0) s_last = arrive(a.counter) == (unsigned)(TRIAL ? nblk : a.gv_blocks + 1) - 1u;
   }
   __syncthreads();
   if (!s_last) return;
@@ -189,7 +180,7 @@ __device__ __forceinline__ void finish_body(const FinishArgs& a, const int bx, c
   if (tid < 4) v7[3] = get_agent(a.fpart + (int64_t)(nblk - 1) * 4 + tid);
 #pragma unroll
   for (int e = 0; e < 3; ++e) {
-    v7[e] = rpca_cols::wave_sum63(v7[e]);
+    v7[e] = wave_sum63(v7[e]);
     if (lane == 63) sPart[w][e] = v7[e];
   }
   if (tid < 4) sPart[0][3 + tid] = v7[3];

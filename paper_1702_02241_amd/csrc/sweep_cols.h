@@ -50,6 +50,7 @@
 #include <type_traits>
 
 #include "rpca_internal.h"
+#include "wave_sum.h"
 
 namespace rpca_cols {
 
@@ -173,25 +174,6 @@ __device__ __forceinline__ float huber(float Rn, float lam_s, float kappa, bool 
   return gn;
 }
 
-// Sum over the wave's 64 lanes in a fixed order (row shifts, then the row broadcasts of
-// the data-parallel primitives: no LDS round trips); the total is in lane 63.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_add(double v) {
-  const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWS, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, ROWS, 0xF, false);
-  return v + __builtin_bit_cast(double, ((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo);
-}
-__device__ __forceinline__ double wave_sum63(double v) {
-  v = dpp_add<0x111, 0xF>(v);  // row_shr:1
-  v = dpp_add<0x112, 0xF>(v);  // row_shr:2
-  v = dpp_add<0x114, 0xF>(v);  // row_shr:4
-  v = dpp_add<0x118, 0xF>(v);  // row_shr:8
-  v = dpp_add<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
-  v = dpp_add<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
-  return v;
-}
-
 // KQ = residual steps of four ranks (k <= 4 KQ): 3 or 4 for k <= 16, 6 to 8 above.
 template <int KQ, bool MASKED, bool TRIAL, bool BF16, bool ELASTIC>
 __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, const int ch, float* lds, double* sRed) {
@@ -204,9 +186,13 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
   float alpha = 0.f;
   if (TRIAL) {
     const SolverState* st = a.st;
-    if (st->phase != PH_TRIAL) return;
+    const int phase = st->phase;
+    const double al = st->alpha;
     cur = st->cur;
-    alpha = (float)st->alpha;
+    LOADED(phase, cur);
+    asm volatile("" ::"s"(al));
+    if (phase != PH_TRIAL) return;
+    alpha = (float)al;
     outi = 1 - cur;
   }
   const int tid = threadIdx.x, lane = tid & 63;
