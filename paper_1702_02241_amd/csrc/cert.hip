@@ -30,6 +30,7 @@
 #include <vector>
 
 #include "rpca_internal.h"
+#include "rows_gram.h"
 #include "ritz_kernel.h"
 #include "smalllinalg.h"
 
@@ -571,45 +572,32 @@ struct GramArgs {
   double* part;  // [blocks][w*w]
 };
 
+template <int NB, int MODE>
 __global__ __launch_bounds__(THREADS) void k_gram(GramArgs a) {
-  constexpr int TR = 32;
-  __shared__ double tile[TR][64];
-  const int w = a.w, ww = w * w;
-  double acc[16];
+  static_assert(THREADS == rpca_rows::TH, "block size");
+  double* part = a.part + (int64_t)blockIdx.x * a.w * a.w;
+  const int li = threadIdx.x & 15;
+  if constexpr (MODE == 0) {
+    const double lam = (double)a.lam;
+    rpca_rows::rows_gram<NB, 2>(a.rows, a.k, a.k, [&](int64_t o, double(&x)[NB]) {
+      float u[NB / 2], g[NB / 2];
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.0;
-  for (int64_t r0 = (int64_t)blockIdx.x * TR; r0 < a.rows; r0 += (int64_t)gridDim.x * TR) {
-    for (int idx = threadIdx.x; idx < TR * w; idx += THREADS) {
-      const int rr = idx / w, cc = idx % w;
-      const int64_t i = r0 + rr;
-      double v = 0.0;
-      if (i < a.rows) {
-        if (a.mode == 0) {
-          if (cc < a.k) v = a.A[i * a.k + cc];
-          else v = (double)a.B[i * a.k + cc - a.k] - (double)a.lam * (double)a.A[i * a.k + cc - a.k];
-        } else {
-          v = a.D[i * a.ldd + cc];
-        }
+      for (int i = 0; i < NB / 2; ++i) {
+        const int c = 16 * i + li < a.k ? 16 * i + li : 0;
+        u[i] = a.A[o + c];
+        g[i] = a.B[o + c];
       }
-      tile[rr][cc] = v;
-    }
-    __syncthreads();
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int idx = threadIdx.x + e * THREADS;
-      if (idx < ww) {
-        const int p = idx / w, q = idx % w;
-        double s = acc[e];
-        for (int rr = 0; rr < TR; ++rr) s = fma(tile[rr][p], tile[rr][q], s);
-        acc[e] = s;
+      for (int i = 0; i < NB / 2; ++i) {
+        x[i] = u[i];
+        x[NB / 2 + i] = (double)g[i] - lam * (double)u[i];
       }
-    }
-    __syncthreads();
-  }
+    }, part);
+  } else {
+    rpca_rows::rows_gram<NB, 1>(a.rows, a.ldd, a.w, [&](int64_t o, double(&x)[NB]) {
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int idx = threadIdx.x + e * THREADS;
-    if (idx < ww) a.part[(int64_t)blockIdx.x * ww + idx] = acc[e];
+      for (int i = 0; i < NB; ++i) x[i] = a.D[o + (16 * i + li < a.w ? 16 * i + li : 0)];
+    }, part);
   }
 }
 
@@ -974,7 +962,18 @@ int gram_host(const Workspace& ws, const GramArgs& ga_in, std::vector<double>& o
   GramArgs ga = ga_in;
   ga.part = ws.gram;
   const int blocks = ws.gram_blocks;
-  hipLaunchKernelGGL(k_gram, dim3(blocks), dim3(THREADS), 0, s, ga);
+  if (ga.w < 1 || ga.w > 64) return RPCA_EINVAL;
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(blocks), dim3(THREADS), 0, s, ga); };
+  if (ga.mode == 0) {  // w = 2 k, k <= 32
+    if (ga.k <= 16) go(k_gram<2, 0>);
+    else go(k_gram<4, 0>);
+  } else if (ga.w <= 16) {
+    go(k_gram<1, 1>);
+  } else if (ga.w <= 32) {
+    go(k_gram<2, 1>);
+  } else {
+    go(k_gram<4, 1>);
+  }
   if (hipGetLastError() != hipSuccess) return RPCA_EHIP;
   const int ww = ga.w * ga.w;
   hipLaunchKernelGGL(k_gram_sum, dim3(ww), dim3(THREADS), 0, s, (const double*)ws.gram, blocks, ww, ws.T);

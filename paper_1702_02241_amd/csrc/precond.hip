@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "ctx.h"
+#include "rows_gram.h"
 #include "smalllinalg.h"
 
 namespace {
@@ -31,33 +32,15 @@ namespace {
 constexpr int TH = 256;
 
 // Per-block partial Gram matrices of the rows of an FP32 row-major matrix
-// (rows x k, k <= 32), FP64: part[blockIdx][k*k].
-__global__ __launch_bounds__(TH) void k_gram_rows(const float* A, int64_t rows, int k, double* part) {
-  constexpr int TR = 64;
-  __shared__ float tile[TR * 32];
-  const int kk2 = k * k;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int64_t r0 = (int64_t)blockIdx.x * TR; r0 < rows; r0 += (int64_t)gridDim.x * TR) {
-    const int nr = (int)((rows - r0) < TR ? (rows - r0) : TR);
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < nr * k; idx += TH) tile[idx] = A[r0 * k + idx];
-    __syncthreads();
+// (rows x k, k <= 16 NB), FP64: part[blockIdx][k*k].
+template <int NB>
+__global__ __launch_bounds__(TH) void k_gram_rows(const float* __restrict__ A, int64_t rows, int k, double* part) {
+  static_assert(TH == rpca_rows::TH, "block size");
+  const int li = threadIdx.x & 15;
+  rpca_rows::rows_gram<NB, 1>(rows, k, k, [&](int64_t o, double(&x)[NB]) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int idx = threadIdx.x + e * TH;
-      if (idx < kk2) {
-        const int p = idx / k, q = idx % k;
-        double sacc = 0.0;
-        for (int rr = 0; rr < nr; ++rr) sacc = fma((double)tile[rr * k + p], (double)tile[rr * k + q], sacc);
-        acc[e] += sacc;
-      }
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int idx = threadIdx.x + e * TH;
-    if (idx < kk2) part[(int64_t)blockIdx.x * kk2 + idx] = acc[e];
-  }
+    for (int i = 0; i < NB; ++i) x[i] = A[o + (16 * i + li < k ? 16 * i + li : 0)];
+  }, part + (int64_t)blockIdx.x * k * k);
 }
 
 // In place, row by row: A_i <- A_i T  (A: rows x k FP32 row-major; T: k x k FP32 row-major).
@@ -105,7 +88,8 @@ int gram(rpca_ctx* c, const float* A, int64_t rows, std::vector<double>& out, hi
   const int kk2 = k * k;
   int64_t blocks = (rows + 63) / 64;
   if (blocks > rpca::PC_GRAM_BLOCKS) blocks = rpca::PC_GRAM_BLOCKS;
-  hipLaunchKernelGGL(k_gram_rows, dim3((unsigned)blocks), dim3(TH), 0, s, A, rows, k, c->pc_gram);
+  if (k <= 16) hipLaunchKernelGGL(k_gram_rows<1>, dim3((unsigned)blocks), dim3(TH), 0, s, A, rows, k, c->pc_gram);
+  else hipLaunchKernelGGL(k_gram_rows<2>, dim3((unsigned)blocks), dim3(TH), 0, s, A, rows, k, c->pc_gram);
   if (hipGetLastError() != hipSuccess) return RPCA_EHIP;
   double* sum = c->pc_gram + (size_t)rpca::PC_GRAM_BLOCKS * kk2;
   hipLaunchKernelGGL(k_gram_rows_sum, dim3((unsigned)kk2), dim3(TH), 0, s, (const double*)c->pc_gram, (int)blocks,
