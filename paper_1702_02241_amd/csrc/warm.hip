@@ -18,6 +18,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "rpca.h"
@@ -65,15 +66,17 @@ __device__ __forceinline__ float epilogue(const GemmArgs& a, int64_t i, int64_t 
 // operands and the output agree, so every load is 16 contiguous bytes:
 //   KMAJ (element (x, k) at p[k ld + x]): row k, x = x0 + 4 li + t -- tile t holds x0 + 4 i + t
 //   else (p[x ld + k]): row x = x0 + 16 t + li, four K values -- tile t holds x0 + 16 t + i
-// Elements past X or kend read as zero.
-template <bool KMAJ>
+// Elements past X or kend read as zero.  SEQ: K = k0 + 4 q + lk instead, so that the products
+// run through K in order (the rows of a non-KMAJ operand then take four loads of 4 bytes).
+template <bool KMAJ, bool SEQ>
 __device__ __forceinline__ void load_operand(const float* __restrict__ p, int64_t ld, int64_t x0, int64_t X, int64_t k0,
                                              int64_t kend, int li, int lk, float (&o)[4][4]) {
+  auto kof = [&](int q) -> int64_t { return k0 + (SEQ ? 4 * q + lk : 4 * lk + q); };
   if (KMAJ) {
     if (x0 + 64 <= X && k0 + BK <= kend) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const f4 v = *reinterpret_cast<const f4u*>(p + (k0 + 4 * lk + q) * ld + x0 + 4 * li);
+        const f4 v = *reinterpret_cast<const f4u*>(p + kof(q) * ld + x0 + 4 * li);
 #pragma unroll
         for (int t = 0; t < 4; ++t) o[t][q] = v[t];
       }
@@ -82,7 +85,7 @@ __device__ __forceinline__ void load_operand(const float* __restrict__ p, int64_
       for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-          const int64_t k = k0 + 4 * lk + q, x = x0 + 4 * li + t;
+          const int64_t k = kof(q), x = x0 + 4 * li + t;
           o[t][q] = (k < kend && x < X) ? p[k * ld + x] : 0.f;
         }
     }
@@ -90,7 +93,9 @@ __device__ __forceinline__ void load_operand(const float* __restrict__ p, int64_
     if (x0 + 64 <= X && k0 + BK <= kend) {
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        const f4 v = *reinterpret_cast<const f4u*>(p + (x0 + 16 * t + li) * ld + k0 + 4 * lk);
+        const float* row = p + (x0 + 16 * t + li) * ld;
+        const f4 v = SEQ ? f4{row[kof(0)], row[kof(1)], row[kof(2)], row[kof(3)]}
+                         : f4(*reinterpret_cast<const f4u*>(row + k0 + 4 * lk));
 #pragma unroll
         for (int q = 0; q < 4; ++q) o[t][q] = v[q];
       }
@@ -99,7 +104,7 @@ __device__ __forceinline__ void load_operand(const float* __restrict__ p, int64_
       for (int t = 0; t < 4; ++t)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int64_t k = k0 + 4 * lk + q, x = x0 + 16 * t + li;
+          const int64_t k = kof(q), x = x0 + 16 * t + li;
           o[t][q] = (k < kend && x < X) ? p[x * ld + k] : 0.f;
         }
     }
@@ -113,17 +118,21 @@ __device__ __forceinline__ void load_operand(const float* __restrict__ p, int64_
 // are 20 us each at the matrix unit's rate.
 //
 // op(A) is KMAJ when TA, op(B) when !TB.  WK = 4: the workgroup's waves split the K range
-// of one tile and meet in LDS; WK = 1 (K of a few blocks): each wave has its own tile.
+// of one tile and meet in LDS; WK = 1 (K of a few blocks): each wave has its own tile;
+// WK = 0: each wave takes a K range of its own through K in order and writes it as a partial
+// (or the result, if there is one range), so an entry's rounding depends on the ranges alone.
 template <bool TA, bool TB, int WK>
 __global__ __launch_bounds__(GT) void k_gemm(GemmArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4;
   const int64_t m0 = (int64_t)blockIdx.y * BM, n0 = ((int64_t)blockIdx.x * (WK == 1 ? 4 : 1) + (WK == 1 ? w : 0)) * BN;
-  const int64_t kbeg = ((int64_t)blockIdx.z * WK + (WK == 1 ? 0 : w)) * a.kchunk;
+  const int64_t z = WK == 0 ? (int64_t)blockIdx.z * 4 + w : blockIdx.z;  // partial
+  const int64_t kbeg = (WK == 4 ? z * 4 + w : z) * a.kchunk;
   int64_t kend = kbeg + a.kchunk;
   if (kend > a.K) kend = a.K;
   if (WK == 1 && n0 >= a.N) return;
+  if (WK == 0 && kbeg >= a.K) return;
   f4 acc[4][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -132,14 +141,14 @@ __global__ __launch_bounds__(GT) void k_gemm(GemmArgs a) {
 
   if (kbeg < kend) {
     float av[4][4], bv[4][4];
-    load_operand<TA>(a.A, a.lda, m0, a.M, kbeg, kend, li, lk, av);
-    load_operand<!TB>(a.B, a.ldb, n0, a.N, kbeg, kend, li, lk, bv);
+    load_operand<TA, WK == 0>(a.A, a.lda, m0, a.M, kbeg, kend, li, lk, av);
+    load_operand<!TB, WK == 0>(a.B, a.ldb, n0, a.N, kbeg, kend, li, lk, bv);
     for (int64_t k0 = kbeg; k0 < kend; k0 += BK) {
       float an[4][4], bn[4][4];
       const bool more = k0 + BK < kend;
       if (more) {
-        load_operand<TA>(a.A, a.lda, m0, a.M, k0 + BK, kend, li, lk, an);
-        load_operand<!TB>(a.B, a.ldb, n0, a.N, k0 + BK, kend, li, lk, bn);
+        load_operand<TA, WK == 0>(a.A, a.lda, m0, a.M, k0 + BK, kend, li, lk, an);
+        load_operand<!TB, WK == 0>(a.B, a.ldb, n0, a.N, k0 + BK, kend, li, lk, bn);
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q)
@@ -163,7 +172,7 @@ __global__ __launch_bounds__(GT) void k_gemm(GemmArgs a) {
   auto put = [&](int i, int r, const f4& v) {  // v[j]: the four N tiles
     const int64_t gm = row(i, r);
     if (gm >= a.M) return;
-    float* dst = a.part ? a.part + (int64_t)blockIdx.z * a.M * a.N + gm * a.N : a.C + gm * a.ldc;
+    float* dst = a.part ? a.part + z * a.M * a.N + gm * a.N : a.C + gm * a.ldc;
     const int64_t gn = n0 + (TB ? li : 4 * li);
     if (!TB && gn + 4 <= a.N) {
       f4 o = v;
@@ -179,7 +188,7 @@ __global__ __launch_bounds__(GT) void k_gemm(GemmArgs a) {
       if (g < a.N) dst[g] = a.part ? v[j] : epilogue(a, gm, g, v[j]);
     }
   };
-  if (WK == 1) {
+  if (WK != 4) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -710,6 +719,30 @@ struct rpca_mlp {
 
 namespace {
 
+// The first layer's product for more than MV rows, through K in ranges and in an order that
+// depend on the sizes alone and stay as they are: a hidden unit's gate in the backward pass
+// is the sign of this sum, so another order of the same additions now and then turns a unit
+// whose input is zero to rounding on or off (one in 32,768 moved grad W1 by 2e-3 relative).
+hipError_t gemm_in_order(rpca_mlp* net, GemmArgs g, hipStream_t s) {
+  const int64_t tm = (g.M + BM - 1) / BM, tn = (g.N + BN - 1) / BN, tiles = tm * tn;
+  const int64_t kslices = (g.K + BK - 1) / BK;
+  int64_t splits = 1;
+  if (tiles < 512 && kslices >= 8) {
+    splits = std::min((512 + tiles - 1) / tiles, kslices / 4);
+    splits = std::max<int64_t>(1, std::min(splits, net->part_cap / (g.M * g.N)));
+  }
+  g.kchunk = (kslices + splits - 1) / splits * BK;
+  splits = (g.K + g.kchunk - 1) / g.kchunk;
+  g.part = splits > 1 ? net->part : nullptr;
+  if (tm > 65535 || splits > 65535) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_gemm<false, false, 0>), dim3((unsigned)tn, (unsigned)tm, (unsigned)((splits + 3) / 4)),
+                     dim3(GT), 0, s, g);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || splits == 1) return e;
+  hipLaunchKernelGGL(k_splitk_reduce, dim3(grid_for(g.M * g.N)), dim3(GT), 0, s, g, (int)splits);
+  return hipGetLastError();
+}
+
 // Launch C = op(A) op(B) with the epilogue in `e` (A, B, C, sizes filled by the caller).
 hipError_t gemm(rpca_mlp* net, GemmArgs g, bool ta, bool tb, hipStream_t s) {
   const int64_t cap = net->part_cap / (g.M * g.N);
@@ -814,7 +847,7 @@ hipError_t forward_into(rpca_mlp* n, const float* x, int batch, float* y, hipStr
   GemmArgs g1 = gemm_args(x, n->d_in, n->param[0], n->d_h, n->h, n->d_h, batch, n->d_h, n->d_in);
   g1.bias = n->param[1];
   g1.relu = 1;
-  hipError_t e = gemm(n, g1, false, false, s);
+  hipError_t e = batch > MV ? gemm_in_order(n, g1, s) : gemm(n, g1, false, false, s);
   if (e != hipSuccess) return e;
   GemmArgs g2 = gemm_args(n->h, n->d_h, n->param[2], n->d_out, y, n->d_out, batch, n->d_out, n->d_h);
   g2.bias = n->param[3];
