@@ -25,7 +25,7 @@
 // strip) and VALU work.  The earlier split (whole strips per wave, V operands read from LDS
 // for every tile, all the chunk's G^T U accumulators in registers) took 32.8 us there at
 // k = 10, 41.5 us as a solver's trial, 31.9 us in BF16, and 371 us at 8192^2, k = 25; this
-// one 26.8, 28.9, 21.5 and 174.  256 x 200: 12.8 to 7.8 us.  Two waves per SIMD and one
+// one 26.0, 29.4, 21.4 and 165.  256 x 200: 12.8 to 7.8 us.  Two waves per SIMD and one
 // workgroup per compute unit: four waves in 128 registers spilled and took 34.5 to 37 us,
 // with shorter rounds and a barrier each.
 //
@@ -65,7 +65,6 @@ constexpr int TW = 4;                      // most 16-column tiles of a wave
 constexpr int CHUNK_MAX = 16 * TW * WAVES;  // widest column chunk
 constexpr int TS = 20;                     // row stride of a transpose tile (floats)
 constexpr int TSB = 24;                    // the same for bf16 (shorts)
-constexpr int GSTRIPS = 3;                 // strips per group of the G^T U accumulators
 constexpr int NTT = 2;                     // transpose tiles per wave (two tiles in flight)
 constexpr uint32_t BUF_DWORD3 = 0x00020000;  // raw buffer resource word 3 on gfx9 (32-bit data format)
 
@@ -448,24 +447,17 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
         umask[h] = (kk < k ? 0xFFFFu : 0u) | (kk + 1 < k ? 0xFFFF0000u : 0u);
       }
     }
-    // G^T U: gva over the last few strips, gvb over the groups of GSTRIPS before them (short
-    // chains of FP32 additions: one chain over all strips of a workgroup lost precision)
-    f4 gva[NW][KB], gvb[NW][KB];
+    // G^T U over the strips so far, a strip's products summed by themselves first: in one
+    // chain over the strips saturated entries add the same value again and again and round
+    // alike.  28 video starts, gV against 64 bits: 5.9e-8 rms (8.8e-8 with groups of three
+    // strips, 6.7e-8 in the split by strips), at the same speed (8192 x 8192, k = 25,
+    // masked: 165 us for 174); carrying the additions' rounding along as well gave 5.6e-8 for
+    // 8 % more time there
+    f4 gvs[NW][KB];
 #pragma unroll
     for (int t = 0; t < NW; ++t)
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) gva[t][kb] = gvb[t][kb] = f4{0.f, 0.f, 0.f, 0.f};
-    int ngroup = 0;
-    auto close_group = [&]() {
-#pragma unroll
-      for (int t = 0; t < NW; ++t)
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
-          gvb[t][kb] += gva[t][kb];
-          gva[t][kb] = f4{0.f, 0.f, 0.f, 0.f};
-        }
-      ngroup = 0;
-    };
+      for (int kb = 0; kb < KB; ++kb) gvs[t][kb] = f4{0.f, 0.f, 0.f, 0.f};
 
     // strip i of the workgroup (strip li of the round in U buffer ubf) against the wave's
     // tiles; strip inx is requested as the registers fall free
@@ -545,9 +537,13 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) ubb[kb] = *reinterpret_cast<const s4*>(usb + 640 + kb * 256 + lane * 4);
       }
-      f4 gu[KB];
+      f4 gv[NW][KB], gu[KB];
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) gu[kb] = f4{0.f, 0.f, 0.f, 0.f};
+      for (int kb = 0; kb < KB; ++kb) {
+        gu[kb] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < NW; ++t) gv[t][kb] = f4{0.f, 0.f, 0.f, 0.f};
+      }
       float ftile = 0.f, gtile = 0.f;
       const int bsh = 16 * (int)((s_lo + i) & 1) + 4 * g;  // this lane's rows in the mask word
 #pragma unroll
@@ -583,10 +579,10 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
-              for (int kb = 0; kb < KB; ++kb) gva[t][kb] = mfma_f32(x[t][q], ub[kb][q], gva[t][kb]);
+              for (int kb = 0; kb < KB; ++kb) gv[t][kb] = mfma_f32(x[t][q], ub[kb][q], gv[t][kb]);
           } else {
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb) gva[t][kb] = mfma_bf16(Gp[v], ubb[kb], gva[t][kb]);
+            for (int kb = 0; kb < KB; ++kb) gv[t][kb] = mfma_bf16(Gp[v], ubb[kb], gv[t][kb]);
           }
         }
 #pragma unroll
@@ -610,6 +606,10 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
           }
         }
       }
+#pragma unroll
+      for (int t = 0; t < NW; ++t)
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) gvs[t][kb] += gv[t][kb];
       f_acc += ELASTIC ? (double)ftile : (double)ftile - 0.5 * (double)gtile;
       gg_acc += (double)gtile;
       float* dst = sGU + ((li * cgs + cg) * KB) * 256 + lane * 4;
@@ -684,18 +684,16 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
       for (int li = rq; li < spr && i0 + li < nst; li += rqs) {
         const int i = i0 + li, nx = li + rqs < spr ? i + rqs : i1 + rq;
         strip(i, li, ubf, nx);
-        if (++ngroup == GSTRIPS) close_group();
       }
       __syncthreads();
       const bool last = i1 >= nst;
       if (last) {
-        close_group();
         if (rq > 0) {  // the row lanes' accumulators: to lane 0 through LDS
 #pragma unroll
           for (int t = 0; t < NW; ++t)
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
-              *reinterpret_cast<f4*>(sT + ((((rq - 1) * cgs + cg) * TW + t) * KB + kb) * 256 + lane * 4) = gvb[t][kb];
+              *reinterpret_cast<f4*>(sT + ((((rq - 1) * cgs + cg) * TW + t) * KB + kb) * 256 + lane * 4) = gvs[t][kb];
         }
       }
       finish_round(i0, ubf);
@@ -721,7 +719,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
       for (int t = 0; t < NW; ++t)
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) {
-          f4 s = gvb[t][kb];
+          f4 s = gvs[t][kb];
           for (int q = 1; q < rqs; ++q)
             s += *reinterpret_cast<const f4*>(sT + ((((q - 1) * cgs + cg) * TW + t) * KB + kb) * 256 + lane * 4);
           const int kk = 16 * kb + c;
