@@ -370,8 +370,8 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
     s4 vgb[BF16 ? NW : 1][KB];
     // A wave without tiles multiplies zeros by zeros: neither the ranks of U nor the rows of V
     // that its operands would hold get in, so an infinity in them stays out of its sums
-    const bool have = NW > 1 || nt > 0;
-    const int kh = have ? k : 0;
+    const bool have = nt > 0;
+    const int kh = NW > 1 || have ? k : 0;
 #pragma unroll
     for (int t = 0; t < NW; ++t) {
       const float* vt = sV + (have ? 16 * (t0 + t) * ks : 0);  // this tile's rows
@@ -406,7 +406,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             const float v = vt[(4 * g + q) * vst + 16 * kb + c];
-            vg[t][kb][q] = have ? v : 0.f;
+            vg[t][kb][q] = NW > 1 || have ? v : 0.f;
           }
       } else {
         if constexpr (KB == 1) {
@@ -440,7 +440,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
         for (int kb = 0; kb < KB; ++kb) {
           const float* q4 = vt + 4 * g * vst + 16 * kb + c;
           vgb[t][kb] = pack_bf16(q4[0], q4[vst], q4[2 * vst], q4[3 * vst]);
-          if (!have) vgb[t][kb] = s4{0, 0, 0, 0};
+          if (NW == 1 && !have) vgb[t][kb] = s4{0, 0, 0, 0};
         }
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -536,7 +536,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
             if (kb == 1) {
               ua[0] &= umask[0];
               ua[1] &= umask[1];
-            } else if (!have) {
+            } else if (NW == 1 && !have) {
               ua = u2v{0u, 0u};
             }
 #pragma unroll
