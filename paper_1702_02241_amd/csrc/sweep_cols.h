@@ -357,7 +357,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
   double f_acc = 0.0, uu_acc = 0.0, gud_acc = 0.0, gg_acc = 0.0;
 
   // Everything that holds the wave's tiles in registers, for a wave of NW tiles (nt, or one
-  // empty tile if it has none): the tile loops carry no branches; the waves of a workgroup
+  // that is never used if it has none): the tile loops carry no branches; the waves of a workgroup
   // run different instantiations and meet at the same barriers.
   auto run = [&](auto nwc) {
     constexpr int NW = decltype(nwc)::value;
@@ -368,10 +368,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
     u4v vrb[BF16 && KB == 1 ? NW : 1][2];   // BF16, k <= 16: hi/lo blocks of eight ranks
     s4 vrs[BF16 && KB == 2 ? NW : 1][KB];   // BF16, k > 16
     s4 vgb[BF16 ? NW : 1][KB];
-    // A wave without tiles multiplies zeros by zeros: neither the ranks of U nor the rows of V
-    // that its operands would hold get in, so an infinity in them stays out of its sums
     const bool have = nt > 0;
-    const int kh = NW > 1 || have ? k : 0;
 #pragma unroll
     for (int t = 0; t < NW; ++t) {
       const float* vt = sV + (have ? 16 * (t0 + t) * ks : 0);  // this tile's rows
@@ -404,10 +401,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const float v = vt[(4 * g + q) * vst + 16 * kb + c];
-            vg[t][kb][q] = NW > 1 || have ? v : 0.f;
-          }
+          for (int q = 0; q < 4; ++q) vg[t][kb][q] = vt[(4 * g + q) * vst + 16 * kb + c];
       } else {
         if constexpr (KB == 1) {
 #pragma unroll
@@ -440,7 +434,6 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
         for (int kb = 0; kb < KB; ++kb) {
           const float* q4 = vt + 4 * g * vst + 16 * kb + c;
           vgb[t][kb] = pack_bf16(q4[0], q4[vst], q4[2 * vst], q4[3 * vst]);
-          if (NW == 1 && !have) vgb[t][kb] = s4{0, 0, 0, 0};
         }
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -451,7 +444,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
 #pragma unroll
       for (int h = 0; h < 4; ++h) {
         const int kk = KB == 1 ? 8 + 2 * h : 16 + 4 * g + 2 * (h & 1);
-        umask[h] = (kk < kh ? 0xFFFFu : 0u) | (kk + 1 < kh ? 0xFFFF0000u : 0u);
+        umask[h] = (kk < k ? 0xFFFFu : 0u) | (kk + 1 < k ? 0xFFFF0000u : 0u);
       }
     }
     // G^T U over the strips so far, a strip's products summed by themselves first: in one
@@ -469,6 +462,12 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
     // strip i of the workgroup (strip li of the round in U buffer ubf) against the wave's
     // tiles; strip inx is requested as the registers fall free
     auto strip = [&](int i, int li, int ubf, int inx) {
+      if (NW == 1 && nt == 0) {  // no tile: zero sums (zeros times an infinite U or V would not be)
+        float* dst = sGU + ((li * cgs + cg) * KB) * 256 + lane * 4;
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) *reinterpret_cast<f4*>(dst + kb * 256) = f4{0.f, 0.f, 0.f, 0.f};
+        return;
+      }
       if (i >= nfull) {
         // by address: 16 bytes at a time if the strip's rows are all there, else single
         // elements through the transpose tile; the lane index is hidden from the compiler so
@@ -511,7 +510,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
           for (int q = 0; q < 4; ++q) ub[kb][q] = us[(4 * g + q) * ks + 16 * kb + c];
 #pragma unroll
         for (int q = 0; q < KQ; ++q) {
-          ua[q] = 4 * q + g < kh ? ua[q] : 0.f;
+          ua[q] = 4 * q + g < k ? ua[q] : 0.f;
 #pragma unroll
           for (int t = 0; t < NW; ++t) x[t] = mfma_f32(ua[q], vr[t][q], x[t]);
         }
@@ -523,9 +522,9 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
             if (j == 1)
 #pragma unroll
               for (int h = 0; h < 4; ++h) ua[h] &= umask[h];
-            else if (kh < 8)
+            else if (k < 8)
 #pragma unroll
-              for (int h = 0; h < 4; ++h) ua[h] &= (2 * h < kh ? 0xFFFFu : 0u) | (2 * h + 1 < kh ? 0xFFFF0000u : 0u);
+              for (int h = 0; h < 4; ++h) ua[h] &= (2 * h < k ? 0xFFFFu : 0u) | (2 * h + 1 < k ? 0xFFFF0000u : 0u);
 #pragma unroll
             for (int t = 0; t < NW; ++t) x[t] = mfma_bf16x32(ua, vrb[t][j], x[t]);
           }
@@ -536,8 +535,6 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
             if (kb == 1) {
               ua[0] &= umask[0];
               ua[1] &= umask[1];
-            } else if (NW == 1 && !have) {
-              ua = u2v{0u, 0u};
             }
 #pragma unroll
             for (int t = 0; t < NW; ++t) x[t] = mfma_bf16(__builtin_bit_cast(s4, ua), vrs[t][kb], x[t]);
