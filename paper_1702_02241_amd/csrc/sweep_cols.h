@@ -616,7 +616,8 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
       for (int t = 0; t < NW; ++t)
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) gvs[t][kb] += gv[t][kb];
-      f_acc += ELASTIC ? (double)ftile : (double)ftile - 0.5 * (double)gtile;
+      // (past the range of FP32 both sums are infinite, and so is the value: not their difference)
+      f_acc += ELASTIC || gtile == INFINITY ? (double)ftile : (double)ftile - 0.5 * (double)gtile;
       gg_acc += (double)gtile;
       float* dst = sGU + ((li * cgs + cg) * KB) * 256 + lane * 4;
 #pragma unroll

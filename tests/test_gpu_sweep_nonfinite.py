@@ -77,3 +77,27 @@ def test_infinite_factor_entry(m, n, k, mode, where):
     _check(gU.cpu().numpy(), gUr, tol, "gU")
     _check(gV.cpu().numpy(), gVr, tol, "gV")
     ctx.close()
+
+
+@pytest.mark.parametrize("mode", ["plain", "bf16"])
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("val", [np.inf, -np.inf, 3e38])
+@pytest.mark.parametrize("m,n,k", [(128, 80, 26), (300, 144, 20), (512, 528, 25), (256, 200, 10)])
+def test_objective_past_overflow(m, n, k, val, masked, mode):
+    """One huge entry of X and a threshold of 1e20: the entry's value, 1e20 |X|, is past FP32."""
+    p = synth.gaussian_rpca(m=m, n=n, r=5, k=k, seed=m + k)
+    U, V = synth.random_factors(m, n, k, 3 + k, scale=0.5)
+    X = np.array(p.X)
+    X[m // 3, n // 2] = val
+    mask = None
+    if masked:
+        mask = (np.random.default_rng(k).random((m, n)) < 0.7).astype(np.uint8)
+        mask[m // 3, n // 2] = 1
+    dev = device()
+    ctx = T.Context(m, n, k, 1e20, p.lam_l, mask)
+    f, _, _ = ctx.objgrad(T.to_device_X(X, dev), T.to_device_factor(U, dev), T.to_device_factor(V, dev),
+                          R.RPCA_PREC_BF16 if mode == "bf16" else R.RPCA_PREC_FP32)
+    torch.cuda.synchronize()
+    print(f"[overflow {m}x{n} k={k} {val}] f {f.item()}", flush=True)
+    assert f.item() == np.inf
+    ctx.close()
