@@ -93,21 +93,36 @@ void rpca_batch_destroy(rpca_batch* b);
 /* Sweep decomposition table (process-wide), keyed by (k bucket: k <= 8, 16,
  * 24, 32; n bucket: n <= 64, 128, 256, 512, larger).  An entry holds the
  * number of waves the row strips of one sweep are spread over and the
- * divisor of the widest column chunk (512 columns).  Contexts and
+ * divisor of the widest column chunk that fits the LDS budget.  Contexts and
  * batches read the table when they are created, so tune first.
  *
- * rpca_autotune: for every entry, time rpca_objgrad on a synthetic probe
+ * Two kernels read it, each its own entries.  Batches, and contexts with a
+ * wave count of their own, give whole strips to a wave: rpca_tune_get /
+ * rpca_tune_set.  Their chunks have at most 256 columns (fewer above k = 16);
+ * the default is 2048 waves for k <= 16, 1024 above, 4096 above with more than
+ * 512 columns.  A batch takes the chunk divisor as is and the wave count as a
+ * factor (entry / 1024) on the instance's share of the chip's waves; a context
+ * with a wave count takes the divisor alone.  Other contexts split columns:
+ * rpca_tune_get_context / rpca_tune_set_context, chunks of at most 512 columns,
+ * 2048 waves by default.
+ *
+ * rpca_autotune: for every entry of both, time rpca_objgrad on a synthetic probe
  * instance (m_probe rows in [32, 2^24], the bucket's largest k and n) for
  * each candidate (1024, 2048 or 4096 waves x divisor 1 or 2), `reps` calls
  * each (1..10000) on `stream`, and keep the fastest.  Blocks until done.
- * A batch reads both parts of an entry: the chunk divisor as is (of the widest
- * chunk of its own split), and the wave count as a factor on the instance's
- * share of the chip's waves.
- * rpca_tune_get / rpca_tune_set read or overwrite the entry that covers
- * (k, n) (for saving and restoring a tuned table). */
+ *
+ * The get and set functions read or overwrite the entry that covers (k, n)
+ * (for saving and restoring a tuned table).  rpca_tune_set also sets the
+ * context entry, in proportion: the entry's waves over its default, times 2048,
+ * and the same divisor.  A table saved before contexts had entries of their own
+ * is restored with it alone, a full one with rpca_tune_set, then
+ * rpca_tune_set_context (target_waves 1..2^21 there, 64..2^20 in rpca_tune_set;
+ * chunk_div 1..16). */
 int rpca_autotune(int64_t m_probe, int32_t reps, void* stream);
 int rpca_tune_get(int32_t k, int64_t n, int32_t* target_waves, int32_t* chunk_div);
 int rpca_tune_set(int32_t k, int64_t n, int32_t target_waves, int32_t chunk_div);
+int rpca_tune_get_context(int32_t k, int64_t n, int32_t* target_waves, int32_t* chunk_div);
+int rpca_tune_set_context(int32_t k, int64_t n, int32_t target_waves, int32_t chunk_div);
 
 #ifdef __cplusplus
 }

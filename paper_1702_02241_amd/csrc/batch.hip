@@ -386,12 +386,10 @@ int rpca_batch_create(int32_t count, const int64_t* m, const int64_t* n, const i
   }
   for (int i = 0; i < count; ++i) {
     const int64_t nstrips = (m[i] + 15) / 16;
-    // the tuned entry of the instance's (k, n) bucket scales its share and its cap, with
-    // proportionally fewer strips per wave; at the default entry 2 for k <= 16, 1 above, 4
-    // above with more than 512 columns (many chunks, few rows each: 8192 x 8192, k = 25
-    // took 444 us at 1 and 369 at 4)
-    const double tuned =
-        rpca::tune_get(k[i], n[i]).target_waves / (k[i] <= 16 ? 1024.0 : n[i] <= 512 ? 2048.0 : 512.0);
+    // the entry of the instance's (k, n) bucket scales its share and its cap: an
+    // entry that spreads one sweep over more than 1024 waves gives the
+    // instance more waves here too, with proportionally fewer strips each
+    const double tuned = rpca::tune_get(rpca::TUNE_STRIPS, k[i], n[i]).target_waves / 1024.0;
     const int64_t cap = std::max<int64_t>(4, (int64_t)(tuned * (double)nstrips) / BATCH_MIN_STRIPS);
     const int64_t share = llround(BATCH_WAVES_PER_CU * (double)cus * tuned * icost[i] / class_cost[icls[i]]);
     b->waves[i] = (int)std::max<int64_t>(4, std::min<int64_t>(share, cap));

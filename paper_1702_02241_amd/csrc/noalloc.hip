@@ -67,13 +67,14 @@ Layout layout_for(int64_t m, int64_t n, int k, int row_groups, int nchunks, int 
 }
 
 // Whether an instance's size is accepted: the documented limit, which counts the partials
-// of the split by strips over 2,048 waves (k <= 16), 1,024, or 4,096 past 512 columns, sums of
+// of the split by strips at its default entries, sums of
 // 16 of them in 64 bits, and the scalars of their reduction in blocks of 256 threads.  The
-// split in use has wider chunks and needs less; the limit stays where callers rely on it.
+// split in use has wider chunks and needs less; the limit stays where callers rely on it,
+// whatever the tuning table holds.
 bool within_limit(int64_t m, int64_t n, int k) {
   int rows = 0, spw = 0, cw = 0, nch = 0;
-  const int waves = k <= 16 ? 2048 : n > 512 ? 4096 : 1024;
-  const int wgs = rpca::sweep_blocks_for(m, n, k, &rows, &spw, &cw, &nch, waves);
+  const rpca::SweepTune t = rpca::tune_default(rpca::TUNE_STRIPS, rpca::tune_k_bucket(k), rpca::tune_n_bucket(n));
+  const int wgs = rpca::strip_blocks_for(m, n, k, &rows, &spw, &cw, &nch, t);
   const int64_t vrows = 256 / k, ublocks = nch > 1 ? std::min<int64_t>((m * k + 255) / 256, 4096) : 0;
   const size_t blocks = (size_t)((n + vrows - 1) / vrows + ublocks);
   size_t o = align256(16 * sizeof(unsigned)) + align256((size_t)wgs * RPCA_NSCAL * sizeof(double)) +
@@ -93,11 +94,18 @@ extern "C" int rpca_objgrad_noalloc(int64_t m, int64_t n, int32_t k, double lam_
   if (!(lam_s > 0) || !(lam_l > 0) || !isfinite(lam_s) || !isfinite(lam_l)) return RPCA_EINVAL;
   if (m > (int64_t)1 << 31 || n > (int64_t)1 << 24) return RPCA_EINVAL;
   if (!X || !U || !V || !f || !gU || !gV) return RPCA_EINVAL;
-  // the decomposition rpca_create would choose for this instance
+  if (!within_limit(m, n, k)) return RPCA_ETOOBIG;
+  // the decomposition rpca_create would choose for this instance, or the default one if the
+  // tuning table's takes more than the array
   int row_groups = 0, spw = 0, chunk_w = 0, nchunks = 0;
-  const int sweep_wgs = rpca::sweep_blocks_for(m, n, k, &row_groups, &spw, &chunk_w, &nchunks, 0);
-  const Layout L = layout_for(m, n, k, row_groups, nchunks, sweep_wgs);
-  if (!within_limit(m, n, k) || L.total > SCRATCH_BYTES) return RPCA_ETOOBIG;
+  int sweep_wgs = rpca::sweep_blocks_for(m, n, k, &row_groups, &spw, &chunk_w, &nchunks, 0);
+  Layout L = layout_for(m, n, k, row_groups, nchunks, sweep_wgs);
+  if (L.total > SCRATCH_BYTES) {
+    const rpca::SweepTune t = rpca::tune_default(rpca::TUNE_COLS, rpca::tune_k_bucket(k), rpca::tune_n_bucket(n));
+    sweep_wgs = rpca::col_blocks_for(m, n, k, &row_groups, &spw, &chunk_w, &nchunks, t);
+    L = layout_for(m, n, k, row_groups, nchunks, sweep_wgs);
+    if (L.total > SCRATCH_BYTES) return RPCA_ETOOBIG;
+  }
 
   void* base = nullptr;
   if (scratch_address(&base) != hipSuccess) return RPCA_EHIP;

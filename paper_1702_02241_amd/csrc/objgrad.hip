@@ -251,20 +251,20 @@ hipError_t launch_cols_f32(const SweepArgs&, bool, bool, hipStream_t);
 hipError_t launch_cols_bf16(const SweepArgs&, bool, bool, hipStream_t);
 hipError_t launch_cols_f32_elastic(const SweepArgs&, bool, bool, hipStream_t);
 
-// Sweep decomposition table, keyed by (k bucket, n bucket): the number of
+// Sweep decomposition table, keyed by (split, k bucket, n bucket): the number of
 // waves the strips are spread over and the divisor of the widest chunk.
 // Defaults are what measurements at the benchmark shapes favoured; rpca_autotune
-// replaces entries by timing the candidates on the device.
+// replaces entries by timing the candidates of each split on the device.
 // The table is process-wide: reads and writes hold its mutex (contexts of a
 // batch are set up from several host threads).
 namespace {
 struct TuneTable {
   std::mutex mu;
-  SweepTune t[TUNE_KB][TUNE_NB];
+  SweepTune t[TUNE_SPLITS][TUNE_KB][TUNE_NB];
   TuneTable() {
-    // 256 workgroups of eight waves, one per compute unit: what its registers and LDS hold
-    for (int a = 0; a < TUNE_KB; ++a)
-      for (int b = 0; b < TUNE_NB; ++b) t[a][b] = SweepTune{2048, 1};
+    for (int s = 0; s < TUNE_SPLITS; ++s)
+      for (int a = 0; a < TUNE_KB; ++a)
+        for (int b = 0; b < TUNE_NB; ++b) t[s][a][b] = tune_default(s, a, b);
   }
 };
 TuneTable& tune_table() {
@@ -276,24 +276,31 @@ TuneTable& tune_table() {
 int tune_k_bucket(int k) { return k <= 8 ? 0 : k <= 16 ? 1 : k <= 24 ? 2 : 3; }
 int tune_n_bucket(int64_t n) { return n <= 64 ? 0 : n <= 128 ? 1 : n <= 256 ? 2 : n <= 512 ? 3 : 4; }
 
-SweepTune tune_get(int k, int64_t n) {
-  TuneTable& tt = tune_table();
-  std::lock_guard<std::mutex> lock(tt.mu);
-  return tt.t[tune_k_bucket(k)][tune_n_bucket(n)];
+// Columns: 256 workgroups of eight waves, one per compute unit: what its registers and LDS
+// hold.  Strips: workgroups of four waves; k <= 16: two per compute unit; k > 16: one, and for
+// more than 512 columns (many chunks, few rows each) four times as many row groups
+// (8192 x 8192, k = 25, masked: 444 us at 1,024 waves, 369 at 4,096).
+SweepTune tune_default(int split, int kbucket, int nbucket) {
+  if (split == TUNE_COLS) return SweepTune{2048, 1};
+  return SweepTune{kbucket < 2 ? 2048 : nbucket == TUNE_NB - 1 ? 4096 : 1024, 1};
 }
 
-void tune_set(int kbucket, int nbucket, SweepTune t) {
+SweepTune tune_get(int split, int k, int64_t n) {
   TuneTable& tt = tune_table();
   std::lock_guard<std::mutex> lock(tt.mu);
-  tt.t[kbucket][nbucket] = t;
+  return tt.t[split][tune_k_bucket(k)][tune_n_bucket(n)];
+}
+
+void tune_set(int split, int kbucket, int nbucket, SweepTune t) {
+  TuneTable& tt = tune_table();
+  std::lock_guard<std::mutex> lock(tt.mu);
+  tt.t[split][kbucket][nbucket] = t;
 }
 
 // Column chunks (each fitting the sweep's LDS budget) and the wave/workgroup
-// split of the rows of the split by strips, for a given wave count.
+// split of the rows of the split by strips.
 int strip_blocks_for(int64_t m, int64_t n, int k, int* row_groups, int* strips_per_wave, int* chunk_w,
-                     int* nchunks, int target_waves) {
-  SweepTune t = tune_get(k, n);
-  t.target_waves = target_waves;
+                     int* nchunks, SweepTune t) {
   const int kb = (k + 15) / 16;
   int cmax = rpca_sweep::max_chunk(kb, k);
   if (t.chunk_div > 1) cmax = ((cmax / t.chunk_div + 15) / 16) * 16;
@@ -319,14 +326,19 @@ int strip_blocks_for(int64_t m, int64_t n, int k, int* row_groups, int* strips_p
   return (int)(wgs * nch);
 }
 
-// Column chunks (at most 512 columns, cut evenly) and the workgroup split of the rows,
-// from the tuning table's wave count: a workgroup has eight waves and, unless the rows run
-// out, at least one strip per row lane.
-int sweep_blocks_for(int64_t m, int64_t n, int k, int* row_groups, int* strips_per_wave, int* chunk_w,
+int sweep_blocks_for(int64_t m, int64_t n, int k, int* row_groups, int* strips_per_wg, int* chunk_w,
                      int* nchunks, int target_waves) {
-  if (target_waves > 0)
-    return strip_blocks_for(m, n, k, row_groups, strips_per_wave, chunk_w, nchunks, target_waves);
-  const SweepTune t = tune_get(k, n);
+  if (target_waves <= 0)
+    return col_blocks_for(m, n, k, row_groups, strips_per_wg, chunk_w, nchunks, tune_get(TUNE_COLS, k, n));
+  const SweepTune t{target_waves, tune_get(TUNE_STRIPS, k, n).chunk_div};
+  return strip_blocks_for(m, n, k, row_groups, strips_per_wg, chunk_w, nchunks, t);
+}
+
+// Column chunks (at most 512 columns, cut evenly) and the workgroup split of the rows of the
+// split by columns: a workgroup has eight waves and, unless the rows run
+// out, at least one strip per row lane.
+int col_blocks_for(int64_t m, int64_t n, int k, int* row_groups, int* strips_per_lane, int* chunk_w,
+                   int* nchunks, SweepTune t) {
   int cmax = rpca_cols::CHUNK_MAX;
   if (n < cmax) cmax = (int)((n + 15) / 16) * 16;
   if (t.chunk_div > 1) cmax = ((cmax / t.chunk_div + 15) / 16) * 16;
@@ -355,7 +367,7 @@ int sweep_blocks_for(int64_t m, int64_t n, int k, int* row_groups, int* strips_p
   if (wgs < (nstrips + (1 << 21) - 1) >> 21) wgs = (nstrips + (1 << 21) - 1) >> 21;
   const int64_t per_wg = (nstrips + wgs - 1) / wgs;
   *row_groups = (int)wgs;
-  *strips_per_wave = (int)((per_wg + rqs - 1) / rqs);
+  *strips_per_lane = (int)((per_wg + rqs - 1) / rqs);
   *chunk_w = cw;
   *nchunks = nch;
   return (int)(wgs * nch);

@@ -175,17 +175,21 @@ struct LbfgsArgs {
 
 // Host-side launchers (defined in the .hip files).
 namespace rpca {
-// Sweep decomposition per (k bucket, n bucket) (see rpca_autotune).
+// Sweep decomposition per (k bucket, n bucket) (see rpca_autotune), an entry for each of the
+// two splits: the kernels rank the same candidates differently, and their chunks and their
+// workgroups differ.
 constexpr int TUNE_KB = 4;   // k <= 8, 16, 24, 32
 constexpr int TUNE_NB = 5;   // n <= 64, 128, 256, 512, larger
 struct SweepTune {
   int target_waves;  // waves the strips of one sweep are spread over
-  int chunk_div;     // widest LDS-fitting chunk divided by this
+  int chunk_div;     // the split's widest chunk divided by this
 };
+enum { TUNE_STRIPS = 0, TUNE_COLS = 1, TUNE_SPLITS = 2 };
 int tune_k_bucket(int k);
 int tune_n_bucket(int64_t n);
-SweepTune tune_get(int k, int64_t n);
-void tune_set(int kbucket, int nbucket, SweepTune t);
+SweepTune tune_default(int split, int kbucket, int nbucket);
+SweepTune tune_get(int split, int k, int64_t n);
+void tune_set(int split, int kbucket, int nbucket, SweepTune t);
 // Sweep decomposition of an m x n, rank-k instance: the split by columns, from the tuning
 // table, or for target_waves > 0 the split by strips over that many waves (a batch spreads
 // one chip's waves over many instances).  An explicit wave count keeps the split by strips
@@ -194,6 +198,11 @@ void tune_set(int kbucket, int nbucket, SweepTune t);
 // in the factors.
 int sweep_blocks_for(int64_t m, int64_t n, int k, int* row_groups, int* strips_per_wg, int* chunk_w,
                      int* nchunks, int target_waves = 0);
+// The same of either split from a given entry.
+int strip_blocks_for(int64_t m, int64_t n, int k, int* row_groups, int* strips_per_wave, int* chunk_w,
+                     int* nchunks, SweepTune t);
+int col_blocks_for(int64_t m, int64_t n, int k, int* row_groups, int* strips_per_lane, int* chunk_w,
+                   int* nchunks, SweepTune t);
 // rpca_create with the sweep's wave target given (0: the tuning table's).
 int create_ctx(int64_t m, int64_t n, int32_t k, double lam_s, double lam_l, const uint8_t* mask,
                int target_waves, rpca_ctx** out, const uint32_t* mask_bits_dev = nullptr);

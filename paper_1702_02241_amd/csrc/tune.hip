@@ -2,7 +2,8 @@
 // the table it builds a probe instance (m_probe rows, the bucket's largest
 // k and n, seeded synthetic X and factors generated on the device), times
 // rpca_objgrad with HIP events for each candidate (waves the strips are
-// spread over x divisor of the widest chunk) and keeps the fastest.
+// spread over x divisor of the widest chunk) and keeps the fastest, for the split by strips
+// and the split by columns in turn.
 #include <math.h>
 
 #include "rpca_internal.h"
@@ -24,8 +25,22 @@ __global__ void k_fill(float* p, int64_t n, uint64_t seed, float scale) {
 
 const int K_REP[rpca::TUNE_KB] = {8, 16, 24, 32};
 const int64_t N_REP[rpca::TUNE_NB] = {64, 128, 256, 512, 1024};
-const int WAVE_CAND[] = {1024, 2048, 4096};
-const int DIV_CAND[] = {1, 2};
+constexpr int N_WAVE = 3, N_DIV = 2;
+const int WAVE_CAND[N_WAVE] = {1024, 2048, 4096};
+const int DIV_CAND[N_DIV] = {1, 2};
+
+bool entry_ok(int32_t k, int64_t n, int32_t target_waves, int32_t chunk_div) {
+  return k >= 1 && k <= 32 && n >= 1 && target_waves >= 64 && target_waves <= (1 << 20) && chunk_div >= 1 &&
+         chunk_div <= 16;
+}
+
+int get_entry(int split, int32_t k, int64_t n, int32_t* target_waves, int32_t* chunk_div) {
+  if (k < 1 || k > 32 || n < 1 || !target_waves || !chunk_div) return RPCA_EINVAL;
+  const rpca::SweepTune t = rpca::tune_get(split, k, n);
+  *target_waves = t.target_waves;
+  *chunk_div = t.chunk_div;
+  return RPCA_OK;
+}
 
 }  // namespace
 
@@ -54,35 +69,35 @@ int rpca_autotune(int64_t m_probe, int32_t reps, void* stream) {
     hipLaunchKernelGGL(k_fill, dim3(64), dim3(256), 0, s, V, nmax * kmax, 13ull, 0.3f);
     if (hipGetLastError() != hipSuccess) rc = RPCA_EHIP;
   }
-  for (int kb = 0; kb < rpca::TUNE_KB && rc == RPCA_OK; ++kb) {
-    for (int nb = 0; nb < rpca::TUNE_NB && rc == RPCA_OK; ++nb) {
-      const int k = K_REP[kb];
-      const int64_t n = N_REP[nb];
-      float best = INFINITY;
-      rpca::SweepTune best_t{2048, 1};
-      for (int w : WAVE_CAND) {
-        for (int d : DIV_CAND) {
-          rpca::tune_set(kb, nb, rpca::SweepTune{w, d});
-          rpca_ctx* c = nullptr;
-          if ((rc = rpca_create(m_probe, n, k, 0.1, 1.0, nullptr, &c)) != RPCA_OK) break;
-          for (int r = 0; r < 2 && rc == RPCA_OK; ++r) rc = rpca_objgrad(c, X, U, V, f, gU, gV, s);
-          if (rc == RPCA_OK && hipEventRecord(e0, s) != hipSuccess) rc = RPCA_EHIP;
-          for (int r = 0; r < reps && rc == RPCA_OK; ++r) rc = rpca_objgrad(c, X, U, V, f, gU, gV, s);
-          float ms = INFINITY;
-          if (rc == RPCA_OK && (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
-                                hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
-            rc = RPCA_EHIP;
-          rpca_destroy(c);
-          if (rc != RPCA_OK) break;
-          if (ms < best) {
-            best = ms;
-            best_t = rpca::SweepTune{w, d};
-          }
-        }
-        if (rc != RPCA_OK) break;
+  for (int e = 0; e < rpca::TUNE_SPLITS * rpca::TUNE_KB * rpca::TUNE_NB && rc == RPCA_OK; ++e) {
+    const int split = e / (rpca::TUNE_KB * rpca::TUNE_NB), kb = e / rpca::TUNE_NB % rpca::TUNE_KB, nb = e % rpca::TUNE_NB;
+    const int k = K_REP[kb];
+    const int64_t n = N_REP[nb];
+    float best = INFINITY;
+    rpca::SweepTune best_t = rpca::tune_get(split, k, n);  // stays if a candidate fails
+    const rpca::SweepTune before = best_t;
+    for (int cand = 0; cand < N_WAVE * N_DIV && rc == RPCA_OK; ++cand) {
+      const rpca::SweepTune t{WAVE_CAND[cand / N_DIV], DIV_CAND[cand % N_DIV]};
+      rpca::tune_set(split, kb, nb, t);
+      rpca_ctx* c = nullptr;
+      // a context of the split whose entry this is
+      if ((rc = rpca_create_waves(m_probe, n, k, 0.1, 1.0, nullptr, split == rpca::TUNE_STRIPS ? t.target_waves : 0,
+                                  &c)) != RPCA_OK)
+        break;
+      for (int r = 0; r < 2 && rc == RPCA_OK; ++r) rc = rpca_objgrad(c, X, U, V, f, gU, gV, s);
+      if (rc == RPCA_OK && hipEventRecord(e0, s) != hipSuccess) rc = RPCA_EHIP;
+      for (int r = 0; r < reps && rc == RPCA_OK; ++r) rc = rpca_objgrad(c, X, U, V, f, gU, gV, s);
+      float ms = INFINITY;
+      if (rc == RPCA_OK && (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
+                            hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
+        rc = RPCA_EHIP;
+      rpca_destroy(c);
+      if (rc == RPCA_OK && ms < best) {
+        best = ms;
+        best_t = t;
       }
-      rpca::tune_set(kb, nb, best_t);
     }
+    rpca::tune_set(split, kb, nb, rc == RPCA_OK ? best_t : before);
   }
   if (X) (void)hipFree(X);
   if (U) (void)hipFree(U);
@@ -96,17 +111,29 @@ int rpca_autotune(int64_t m_probe, int32_t reps, void* stream) {
 }
 
 int rpca_tune_get(int32_t k, int64_t n, int32_t* target_waves, int32_t* chunk_div) {
-  if (k < 1 || k > 32 || n < 1 || !target_waves || !chunk_div) return RPCA_EINVAL;
-  const rpca::SweepTune t = rpca::tune_get(k, n);
-  *target_waves = t.target_waves;
-  *chunk_div = t.chunk_div;
-  return RPCA_OK;
+  return get_entry(rpca::TUNE_STRIPS, k, n, target_waves, chunk_div);
 }
 
 int rpca_tune_set(int32_t k, int64_t n, int32_t target_waves, int32_t chunk_div) {
-  if (k < 1 || k > 32 || n < 1 || target_waves < 64 || target_waves > (1 << 20) || chunk_div < 1 || chunk_div > 16)
+  if (!entry_ok(k, n, target_waves, chunk_div)) return RPCA_EINVAL;
+  const int kb = rpca::tune_k_bucket(k), nb = rpca::tune_n_bucket(n);
+  rpca::tune_set(rpca::TUNE_STRIPS, kb, nb, rpca::SweepTune{target_waves, chunk_div});
+  // contexts follow in proportion: a default entry means the default there too
+  const int64_t w = (int64_t)target_waves * rpca::tune_default(rpca::TUNE_COLS, kb, nb).target_waves /
+                    rpca::tune_default(rpca::TUNE_STRIPS, kb, nb).target_waves;
+  rpca::tune_set(rpca::TUNE_COLS, kb, nb, rpca::SweepTune{(int)w, chunk_div});
+  return RPCA_OK;
+}
+
+int rpca_tune_get_context(int32_t k, int64_t n, int32_t* target_waves, int32_t* chunk_div) {
+  return get_entry(rpca::TUNE_COLS, k, n, target_waves, chunk_div);
+}
+
+int rpca_tune_set_context(int32_t k, int64_t n, int32_t target_waves, int32_t chunk_div) {
+  if (k < 1 || k > 32 || n < 1 || target_waves < 1 || target_waves > (1 << 21) || chunk_div < 1 || chunk_div > 16)
     return RPCA_EINVAL;
-  rpca::tune_set(rpca::tune_k_bucket(k), rpca::tune_n_bucket(n), rpca::SweepTune{target_waves, chunk_div});
+  rpca::tune_set(rpca::TUNE_COLS, rpca::tune_k_bucket(k), rpca::tune_n_bucket(n),
+                 rpca::SweepTune{target_waves, chunk_div});
   return RPCA_OK;
 }
 

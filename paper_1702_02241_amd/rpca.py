@@ -167,6 +167,8 @@ def lib():
             "rpca_fw_profile_read": (I32, [P, ctypes.POINTER(rpca_fw_profile), I32]),
             "rpca_tune_get": (I32, [I32, I64, ctypes.POINTER(I32), ctypes.POINTER(I32)]),
             "rpca_tune_set": (I32, [I32, I64, I32, I32]),
+            "rpca_tune_get_context": (I32, [I32, I64, ctypes.POINTER(I32), ctypes.POINTER(I32)]),
+            "rpca_tune_set_context": (I32, [I32, I64, I32, I32]),
         }
         for name, (res, args) in sig.items():
             fn = getattr(L, name)
@@ -451,3 +453,13 @@ def rpca_tune_get(k, n):
 
 def rpca_tune_set(k, n, target_waves, chunk_div):
     return lib().rpca_tune_set(k, n, target_waves, chunk_div)
+
+
+def rpca_tune_get_context(k, n):
+    w, d = ctypes.c_int32(), ctypes.c_int32()
+    rc = lib().rpca_tune_get_context(k, n, ctypes.byref(w), ctypes.byref(d))
+    return rc, w.value, d.value
+
+
+def rpca_tune_set_context(k, n, target_waves, chunk_div):
+    return lib().rpca_tune_set_context(k, n, target_waves, chunk_div)
