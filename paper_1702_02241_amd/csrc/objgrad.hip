@@ -339,14 +339,14 @@ int sweep_blocks_for(int64_t m, int64_t n, int k, int* row_groups, int* strips_p
 // out, at least one strip per row lane.
 int col_blocks_for(int64_t m, int64_t n, int k, int* row_groups, int* strips_per_lane, int* chunk_w,
                    int* nchunks, SweepTune t) {
-  int cmax = rpca_cols::CHUNK_MAX;
+  const int64_t nstrips = (m + 15) / 16;
+  int cmax = 16 * rpca_cols::WAVES * rpca_cols::wave_tiles(nstrips);
   if (n < cmax) cmax = (int)((n + 15) / 16) * 16;
   if (t.chunk_div > 1) cmax = ((cmax / t.chunk_div + 15) / 16) * 16;
   int nch = (int)((n + cmax - 1) / cmax);
   int cw = (int)(((n + nch - 1) / nch + 15) / 16) * 16;
   if (cw > cmax) cw = cmax;
   nch = (int)((n + cw - 1) / cw);
-  const int64_t nstrips = (m + 15) / 16;
   // k > 16, and fewer strips than workgroups side by side: narrower chunks, down to a tile
   // per wave (583 x 359, k = 26, masked: 18.6 to 10.9 us; V and the G^T U sums of a wide chunk
   // are most of a workgroup's time there; for k <= 16 they are not, and the further chunks

@@ -93,12 +93,21 @@ __device__ __forceinline__ s4 pack_bf16(float a, float b, float c, float d) {
 __device__ __forceinline__ uint16_t bf16_bits(float x) { return __builtin_bit_cast(uint16_t, (__bf16)x); }
 __device__ __forceinline__ float bf16_val(uint16_t b) { return __builtin_bit_cast(float, (uint32_t)b << 16); }
 
-// Column groups of a chunk: the fewest, a power of two, that leave a wave at most TW tiles;
+// Most tiles of a wave.  Its X is addressed in 32 bits, 64 bytes a row and tile: four tiles
+// below 2^24 rows, two below 2^25 (2^24 x 100, k = 10: 3,103 us; with four, X read by address as
+// it is needed, 3,519).  Longer columns are better read by address, four tiles a wave, than a
+// tile a wave through the resource (2^25 x 100, k = 4: 6,444 us for 7,818), unless one tile is
+// all there is (2^24 x 16, k = 4: 817 us for 1,097).
+__host__ __device__ constexpr int wave_tiles(int64_t nstrips) {
+  return nstrips >= (1 << 20) && nstrips < (1 << 21) ? 2 : TW;
+}
+
+// Column groups of a chunk: the fewest, a power of two, that leave a wave at most that many tiles;
 // twice as many while the strips' waves then still run side by side (2048: two per SIMD) --
 // a wave's strip is shorter, and with one strip per wave nothing else fills the chip.
 __host__ __device__ constexpr int col_groups(int chunk_w, int nchunks, int64_t nstrips) {
-  const int tiles = (chunk_w + 15) / 16;
-  int cgs = tiles <= TW ? 1 : tiles <= 2 * TW ? 2 : tiles <= 4 * TW ? 4 : 8;
+  const int tiles = (chunk_w + 15) / 16, tw = wave_tiles(nstrips);
+  int cgs = tiles <= tw ? 1 : tiles <= 2 * tw ? 2 : tiles <= 4 * tw ? 4 : 8;
   while (cgs < WAVES && cgs < tiles && 2 * cgs * nchunks * nstrips <= 2048) cgs *= 2;
   return cgs;
 }
@@ -312,9 +321,9 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
 
   // ---- X.  Strips whose 16 rows are all inside X read 16-byte pieces through a buffer
   // resource over the wave's columns (columns past the chunk are out of range and read
-  // zero; any 4-byte alignment); the ragged last strip, and columns so long that 64 of them
+  // zero; any 4-byte alignment); the ragged last strip, and columns so long that the wave's
   // pass 32-bit offsets, are read by address
-  const int nfull = m < ((int64_t)1 << 24) ? (nrows >> 4) : 0;
+  const int nfull = nt * m < ((int64_t)1 << 26) ? (nrows >> 4) : 0;
   int vcols = ncols - 16 * t0;
   vcols = vcols < 0 ? 0 : vcols > 16 * nt ? 16 * nt : vcols;
   const int64_t jw = j_begin + 16 * t0;  // first column of the wave
