@@ -72,7 +72,7 @@ __global__ __launch_bounds__(NT, 4) void k_gram_apply(rpca::GramApplyArgs a) {
   const int64_t nst = (s_hi < nstrips ? s_hi : nstrips) - s_lo;
   const int64_t its = (nst + rqs - 1) / rqs;
   const int64_t s_end = s_lo + nst;
-  const int64_t s_full = m < ((int64_t)1 << 24) ? (m >> 4) : 0;  // strips read through the buffer resource
+  const int64_t s_full = nt * m < ((int64_t)1 << 26) ? (m >> 4) : 0;  // strips read through the buffer resource
 
   const int j0 = 16 * t0, vcols = (n - j0 < 16 * nt ? n - j0 : 16 * nt);
   const float* __restrict__ Xw = a.X + j0 * m;
