@@ -25,6 +25,7 @@
 #include <algorithm>
 #include <chrono>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "rpca.h"
@@ -306,7 +307,9 @@ __global__ __launch_bounds__(TH) void k_fw_combine(const float* __restrict__ Y, 
 // over the row's observed entries of v_j^2, in one pass over G and L; block partials of
 // sum y_i z_i and sum y_i^2 q_i (u^T P_Omega(L) v and sum_Omega u_i^2 v_j^2 times sigma and
 // sigma^2, u = y / sigma).  A block of eight waves takes 64 VEC rows, a wave an eighth of
-// the columns (FP32 chains of n / 8, the waves added in order).  Bound by the two reads: at
+// the columns, the waves added in order: y in FP32; z and q in FP32 chains of n / 8 <= 32
+// columns (VEC = 4) or in 64 bits throughout (VEC = 1), the waves' parts in 64 bits, as
+// many FP32 terms as a thread of the bilinear pass sums.  Bound by the two reads: at
 // 76800 x 200 it takes 20.7 us; the left product of the whole block with its chunk sums and
 // combination, and the bilinear pass with its finish, took 15.5 + 6.1 + 4.1 and 12.7 + 3.9.
 constexpr int RW = 8;  // waves per block
@@ -315,14 +318,17 @@ __global__ __launch_bounds__(64 * RW) void k_fw_rows(const float* __restrict__ G
                                                      const float* __restrict__ v, const uint32_t* __restrict__ mask,
                                                      int mw, int64_t m, int n, float* __restrict__ y,
                                                      double* __restrict__ part) {
-  __shared__ float sh[3][RW][64 * VEC];
+  using Sum = typename std::conditional<VEC == 1, double, float>::type;
+  __shared__ float shy[RW][64 * VEC];
+  __shared__ Sum sh[2][RW][64 * VEC];
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t i0 = ((int64_t)blockIdx.x * 64 + lane) * VEC;
   const bool ok = i0 < m;
-  float ay[VEC], az[VEC], aq[VEC];
+  float ay[VEC];
+  Sum az[VEC], aq[VEC];
 #pragma unroll
-  for (int c = 0; c < VEC; ++c) ay[c] = az[c] = aq[c] = 0.f;
+  for (int c = 0; c < VEC; ++c) ay[c] = az[c] = aq[c] = 0;
   if (ok) {
 #pragma unroll 5
     for (int j = w * n / RW; j < (w + 1) * n / RW; ++j) {
@@ -345,29 +351,32 @@ __global__ __launch_bounds__(64 * RW) void k_fw_rows(const float* __restrict__ G
       for (int c = 0; c < VEC; ++c) {
         const bool o = !MASK || ((bits >> c) & 1u);
         ay[c] = fmaf(g[c], vj, ay[c]);  // G is zero where nothing is observed
-        az[c] = o ? fmaf(l[c], vj, az[c]) : az[c];
-        aq[c] = o ? fmaf(vj, vj, aq[c]) : aq[c];
+        az[c] = o ? fma((Sum)l[c], (Sum)vj, az[c]) : az[c];
+        aq[c] = o ? fma((Sum)vj, (Sum)vj, aq[c]) : aq[c];
       }
     }
   }
 #pragma unroll
   for (int c = 0; c < VEC; ++c) {
-    sh[0][w][c * 64 + lane] = ay[c];
-    sh[1][w][c * 64 + lane] = az[c];
-    sh[2][w][c * 64 + lane] = aq[c];
+    shy[w][c * 64 + lane] = ay[c];
+    sh[0][w][c * 64 + lane] = az[c];
+    sh[1][w][c * 64 + lane] = aq[c];
   }
   __syncthreads();
   double s[2] = {0.0, 0.0};
   // wave w: rows of component c = w (VEC = 4) or of wave 0 (VEC = 1)
   if (w < VEC) {
-    float t[3] = {0.f, 0.f, 0.f};
+    float yi = 0.f;
+    double t[2] = {0.0, 0.0};
 #pragma unroll
-    for (int q = 0; q < RW; ++q)
+    for (int q = 0; q < RW; ++q) {
+      yi += shy[q][w * 64 + lane];
 #pragma unroll
-      for (int e = 0; e < 3; ++e) t[e] += sh[e][q][w * 64 + lane];
-    if (ok) y[i0 + w] = t[0];
-    s[0] = (double)t[0] * (double)t[1];
-    s[1] = (double)t[0] * (double)t[0] * (double)t[2];
+      for (int e = 0; e < 2; ++e) t[e] += (double)sh[e][q][w * 64 + lane];
+    }
+    if (ok) y[i0 + w] = yi;
+    s[0] = (double)yi * t[0];
+    s[1] = (double)yi * (double)yi * t[1];
   }
   block_sums<2, 64 * RW>(s, part + (int64_t)blockIdx.x * 2);
 }
