@@ -719,10 +719,11 @@ struct rpca_mlp {
 
 namespace {
 
-// The first layer's product for more than MV rows, through K in ranges and in an order that
+// The first layer's product of a training step, and of more than MV rows, through K in ranges and in an order that
 // depend on the sizes alone and stay as they are: a hidden unit's gate in the backward pass
 // is the sign of this sum, so another order of the same additions now and then turns a unit
 // whose input is zero to rounding on or off (one in 32,768 moved grad W1 by 2e-3 relative).
+// A prediction of at most MV rows has no gates to keep and streams W1 once (k_gemv).
 hipError_t gemm_in_order(rpca_mlp* net, GemmArgs g, hipStream_t s) {
   const int64_t tm = (g.M + BM - 1) / BM, tn = (g.N + BN - 1) / BN, tiles = tm * tn;
   const int64_t kslices = (g.K + BK - 1) / BK;
@@ -843,11 +844,11 @@ GemmArgs gemm_args(const float* A, int64_t lda, const float* B, int64_t ldb, flo
   return g;
 }
 
-hipError_t forward_into(rpca_mlp* n, const float* x, int batch, float* y, hipStream_t s) {
+hipError_t forward_into(rpca_mlp* n, const float* x, int batch, float* y, bool training, hipStream_t s) {
   GemmArgs g1 = gemm_args(x, n->d_in, n->param[0], n->d_h, n->h, n->d_h, batch, n->d_h, n->d_in);
   g1.bias = n->param[1];
   g1.relu = 1;
-  hipError_t e = batch > MV ? gemm_in_order(n, g1, s) : gemm(n, g1, false, false, s);
+  hipError_t e = training || batch > MV ? gemm_in_order(n, g1, s) : gemm(n, g1, false, false, s);
   if (e != hipSuccess) return e;
   GemmArgs g2 = gemm_args(n->h, n->d_h, n->param[2], n->d_out, y, n->d_out, batch, n->d_out, n->d_h);
   g2.bias = n->param[3];
@@ -951,14 +952,14 @@ int rpca_mlp_grad(rpca_mlp* n, int32_t which, float** ptr, int64_t* count) {
 
 int rpca_mlp_forward(rpca_mlp* n, const float* x, int32_t batch, float* y, void* stream) {
   if (!n || !x || !y || batch < 1 || batch > n->max_batch) return RPCA_EINVAL;
-  return forward_into(n, x, batch, y, (hipStream_t)stream) == hipSuccess ? RPCA_OK : RPCA_EHIP;
+  return forward_into(n, x, batch, y, false, (hipStream_t)stream) == hipSuccess ? RPCA_OK : RPCA_EHIP;
 }
 
 int rpca_mlp_loss_grad(rpca_mlp* n, const float* x, const float* TU, const float* TV, int32_t batch,
                        double* loss, void* stream) {
   if (!n || !x || !TU || !TV || !loss || batch < 1 || batch > n->max_batch) return RPCA_EINVAL;
   hipStream_t s = (hipStream_t)stream;
-  if (forward_into(n, x, batch, n->y, s) != hipSuccess) return RPCA_EHIP;
+  if (forward_into(n, x, batch, n->y, true, s) != hipSuccess) return RPCA_EHIP;
   LossArgs l;
   memset(&l, 0, sizeof(l));
   l.y = n->y;
