@@ -19,6 +19,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "rpca.h"
@@ -111,6 +112,28 @@ __device__ __forceinline__ void load_operand(const float* __restrict__ p, int64_
   }
 }
 
+// The same of one 16-wide tile t, with no branch per element: past X or kend the last element
+// is loaded and replaced by zero.
+template <bool KMAJ, bool SEQ>
+__device__ __forceinline__ void load_tile_operand(const float* __restrict__ p, int64_t ld, int64_t x0, int64_t X, int64_t k0,
+                                                  int64_t kend, int li, int lk, int t, float (&o)[4]) {
+  auto kof = [&](int q) -> int64_t { return k0 + (SEQ ? 4 * q + lk : 4 * lk + q); };
+  const int64_t x = x0 + (KMAJ ? 4 * li + t : 16 * t + li), xc = x < X ? x : X - 1;
+  if (!KMAJ && !SEQ && k0 + BK <= kend) {
+    const f4 v = *reinterpret_cast<const f4u*>(p + xc * ld + k0 + 4 * lk);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[q] = v[q];
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t k = kof(q) < kend ? kof(q) : kend - 1;
+      o[q] = KMAJ ? p[k * ld + xc] : p[xc * ld + k];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) o[q] = x < X && kof(q) < kend ? o[q] : 0.f;
+}
+
 // FP32 MFMA-bound (64 products of 32 cycles per 16 loads of a lane): 64 x 64 a wave makes
 // each 16-byte load feed 16 products.  At 64 rows of the 9700-512-49000 network: y = h W2
 // 91 -> 59 us, dz = dy W2^T 158 -> 70 us, dW2 = h^T dy 70 -> 53 us against a 64 x 64
@@ -121,39 +144,51 @@ __device__ __forceinline__ void load_operand(const float* __restrict__ p, int64_
 // of one tile and meet in LDS; WK = 1 (K of a few blocks): each wave has its own tile;
 // WK = 0: each wave takes a K range of its own through K in order and writes it as a partial
 // (or the result, if there is one range), so an entry's rounding depends on the ranges alone.
-template <bool TA, bool TB, int WK>
+// ROWS (WK = 0, 1; products whose tiles and ranges leave most of the chip idle): a workgroup per
+// tile (and range), a 16-row tile of it per wave, with the same sums: a quarter of the products
+// per block of K, and none for rows past M.  300-16-360 at 64 rows, forward: 15.8 us for 32.0,
+// 620-128-2240 at 17: 16.4 for 33.8 (18.0 and 21.9 with 64 x 64 workgroup tiles in LDS).
+template <bool TA, bool TB, int WK, bool ROWS>
 __global__ __launch_bounds__(GT) void k_gemm(GemmArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4;
-  const int64_t m0 = (int64_t)blockIdx.y * BM, n0 = ((int64_t)blockIdx.x * (WK == 1 ? 4 : 1) + (WK == 1 ? w : 0)) * BN;
-  const int64_t z = WK == 0 ? (int64_t)blockIdx.z * 4 + w : blockIdx.z;  // partial
+  static_assert(!ROWS || WK != 4, "the waves share a tile in one way");
+  constexpr int MI = ROWS ? 1 : 4;  // row tiles of a wave
+  constexpr bool NW = WK == 1 && !ROWS;  // the waves take tiles of their own
+  const int64_t m0 = (int64_t)blockIdx.y * BM, n0 = ((int64_t)blockIdx.x * (NW ? 4 : 1) + (NW ? w : 0)) * BN;
+  const int64_t z = WK == 0 && !ROWS ? (int64_t)blockIdx.z * 4 + w : blockIdx.z;  // partial
   const int64_t kbeg = (WK == 4 ? z * 4 + w : z) * a.kchunk;
   int64_t kend = kbeg + a.kchunk;
   if (kend > a.K) kend = a.K;
-  if (WK == 1 && n0 >= a.N) return;
+  if (NW && n0 >= a.N) return;
   if (WK == 0 && kbeg >= a.K) return;
-  f4 acc[4][4];
+  if (ROWS && m0 + (TA ? w : 16 * w) >= a.M) return;  // no row of this wave's tile
+  f4 acc[MI][4];
+  auto load_a = [&](int64_t k0, float (&o)[MI][4]) {
+    if constexpr (ROWS) load_tile_operand<TA, WK == 0>(a.A, a.lda, m0, a.M, k0, kend, li, lk, w, o[0]);
+    else load_operand<TA, WK == 0>(a.A, a.lda, m0, a.M, k0, kend, li, lk, o);
+  };
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
 
   if (kbeg < kend) {
-    float av[4][4], bv[4][4];
-    load_operand<TA, WK == 0>(a.A, a.lda, m0, a.M, kbeg, kend, li, lk, av);
+    float av[MI][4], bv[4][4];
+    load_a(kbeg, av);
     load_operand<!TB, WK == 0>(a.B, a.ldb, n0, a.N, kbeg, kend, li, lk, bv);
     for (int64_t k0 = kbeg; k0 < kend; k0 += BK) {
-      float an[4][4], bn[4][4];
+      float an[MI][4], bn[4][4];
       const bool more = k0 + BK < kend;
       if (more) {
-        load_operand<TA, WK == 0>(a.A, a.lda, m0, a.M, k0 + BK, kend, li, lk, an);
+        load_a(k0 + BK, an);
         load_operand<!TB, WK == 0>(a.B, a.ldb, n0, a.N, k0 + BK, kend, li, lk, bn);
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
           for (int j = 0; j < 4; ++j) acc[i][j] = mfma_f32(av[i][q], bv[j][q], acc[i][j]);
       if (more) {
@@ -161,7 +196,7 @@ __global__ __launch_bounds__(GT) void k_gemm(GemmArgs a) {
         for (int i = 0; i < 4; ++i)
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            av[i][q] = an[i][q];
+            if (i < MI) av[i < MI ? i : 0][q] = an[i < MI ? i : 0][q];
             bv[i][q] = bn[i][q];
           }
       }
@@ -188,11 +223,11 @@ __global__ __launch_bounds__(GT) void k_gemm(GemmArgs a) {
       if (g < a.N) dst[g] = a.part ? v[j] : epilogue(a, gm, g, v[j]);
     }
   };
-  if (WK != 4) {
+  if constexpr (WK != 4) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) put(i, r, f4{acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]});
+      for (int r = 0; r < 4; ++r) put(ROWS ? w : i, r, f4{acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]});
   } else {
     // wave w finishes the row tile i = w: the others' accumulators of it through LDS,
     // added in wave order
@@ -719,6 +754,12 @@ struct rpca_mlp {
 
 namespace {
 
+// Products of fewer tiles (times ranges) than this take a wave per 16 rows (k_gemm's ROWS): with
+// a wave per tile some of the chip's 1,024 SIMDs would have none.  Forward, us, with the
+// line at 0 / 256 / 512 / 1024: 2000-100-29856 at 33 rows 42.4 / 33.5 / 24.5 / 24.6, 9700-512-49000 at
+// 128 rows 129.7 / 129.4 / 129.3 / 113.7.
+constexpr int64_t ROWS_BELOW = 1024;
+
 // The first layer's product of a training step, and of more than MV rows, through K in ranges and in an order that
 // depend on the sizes alone and stay as they are: a hidden unit's gate in the backward pass
 // is the sign of this sum, so another order of the same additions now and then turns a unit
@@ -736,8 +777,11 @@ hipError_t gemm_in_order(rpca_mlp* net, GemmArgs g, hipStream_t s) {
   splits = (g.K + g.kchunk - 1) / g.kchunk;
   g.part = splits > 1 ? net->part : nullptr;
   if (tm > 65535 || splits > 65535) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_gemm<false, false, 0>), dim3((unsigned)tn, (unsigned)tm, (unsigned)((splits + 3) / 4)),
-                     dim3(GT), 0, s, g);
+  if (tiles * splits < ROWS_BELOW)
+    hipLaunchKernelGGL((k_gemm<false, false, 0, true>), dim3((unsigned)tn, (unsigned)tm, (unsigned)splits), dim3(GT), 0, s, g);
+  else
+    hipLaunchKernelGGL((k_gemm<false, false, 0, false>), dim3((unsigned)tn, (unsigned)tm, (unsigned)((splits + 3) / 4)),
+                       dim3(GT), 0, s, g);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || splits == 1) return e;
   hipLaunchKernelGGL(k_splitk_reduce, dim3(grid_for(g.M * g.N)), dim3(GT), 0, s, g, (int)splits);
@@ -747,9 +791,10 @@ hipError_t gemm_in_order(rpca_mlp* net, GemmArgs g, hipStream_t s) {
 // Launch C = op(A) op(B) with the epilogue in `e` (A, B, C, sizes filled by the caller).
 hipError_t gemm(rpca_mlp* net, GemmArgs g, bool ta, bool tb, hipStream_t s) {
   const int64_t cap = net->part_cap / (g.M * g.N);
-  if (!ta && !tb && g.M <= MV) {
+  if (!ta && !tb && g.M <= MV && (g.K >= MV_G || g.M == 1)) {
     // matrix-vector (at most four rows: the predictions of single windows; the tile kernel
-    // pads them to 64 rows and takes 3x as long): 128 (or 32) columns a workgroup, K split until some 512 workgroups are
+    // pads them to 64 rows and takes 3x as long; several rows with fewer values than the K
+    // groups leave groups idle, 64-8-130048 at 4 rows 18.3 us for 13.9 on tiles): 128 (or 32) columns a workgroup, K split until some 512 workgroups are
     // in flight, at least four values a K group
     const bool vec = g.N % 4 == 0 && g.ldb % 4 == 0 && ((uintptr_t)g.B & 15) == 0;
     const int64_t tn = (g.N + MV_L * (vec ? 4 : 1) - 1) / (MV_L * (vec ? 4 : 1));
@@ -776,11 +821,16 @@ hipError_t gemm(rpca_mlp* net, GemmArgs g, bool ta, bool tb, hipStream_t s) {
     // short K (a weight gradient over a small batch): one wave per tile
     g.kchunk = kslices * BK;
     g.part = nullptr;
-    const dim3 grid((unsigned)((tn + 3) / 4), (unsigned)tm, 1);
-    if (!ta && !tb) hipLaunchKernelGGL((k_gemm<false, false, 1>), grid, dim3(GT), 0, s, g);
-    else if (ta && !tb) hipLaunchKernelGGL((k_gemm<true, false, 1>), grid, dim3(GT), 0, s, g);
-    else if (!ta && tb) hipLaunchKernelGGL((k_gemm<false, true, 1>), grid, dim3(GT), 0, s, g);
-    else hipLaunchKernelGGL((k_gemm<true, true, 1>), grid, dim3(GT), 0, s, g);
+    const bool rows = tm * tn < ROWS_BELOW;
+    const dim3 grid((unsigned)(rows ? tn : (tn + 3) / 4), (unsigned)tm, 1);
+    auto go = [&](auto a, auto b) {
+      if (rows) hipLaunchKernelGGL((k_gemm<a(), b(), 1, true>), grid, dim3(GT), 0, s, g);
+      else hipLaunchKernelGGL((k_gemm<a(), b(), 1, false>), grid, dim3(GT), 0, s, g);
+    };
+    if (!ta && !tb) go(std::false_type{}, std::false_type{});
+    else if (ta && !tb) go(std::true_type{}, std::false_type{});
+    else if (!ta && tb) go(std::false_type{}, std::true_type{});
+    else go(std::true_type{}, std::true_type{});
     return hipGetLastError();
   }
   // K over the four waves of a workgroup, then over workgroups until two are resident
@@ -797,10 +847,10 @@ hipError_t gemm(rpca_mlp* net, GemmArgs g, bool ta, bool tb, hipStream_t s) {
   g.part = splits > 1 ? net->part : nullptr;
   if (splits > 65535) return hipErrorInvalidValue;
   const dim3 grid((unsigned)tn, (unsigned)tm, (unsigned)splits);
-  if (!ta && !tb) hipLaunchKernelGGL((k_gemm<false, false, 4>), grid, dim3(GT), 0, s, g);
-  else if (ta && !tb) hipLaunchKernelGGL((k_gemm<true, false, 4>), grid, dim3(GT), 0, s, g);
-  else if (!ta && tb) hipLaunchKernelGGL((k_gemm<false, true, 4>), grid, dim3(GT), 0, s, g);
-  else hipLaunchKernelGGL((k_gemm<true, true, 4>), grid, dim3(GT), 0, s, g);
+  if (!ta && !tb) hipLaunchKernelGGL((k_gemm<false, false, 4, false>), grid, dim3(GT), 0, s, g);
+  else if (ta && !tb) hipLaunchKernelGGL((k_gemm<true, false, 4, false>), grid, dim3(GT), 0, s, g);
+  else if (!ta && tb) hipLaunchKernelGGL((k_gemm<false, true, 4, false>), grid, dim3(GT), 0, s, g);
+  else hipLaunchKernelGGL((k_gemm<true, true, 4, false>), grid, dim3(GT), 0, s, g);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || splits == 1) return e;
   hipLaunchKernelGGL(k_splitk_reduce, dim3(grid_for(g.M * g.N)), dim3(GT), 0, s, g, (int)splits);
