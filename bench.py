@@ -453,7 +453,7 @@ def run_partial(args):
         "config": {"workload": "m=n=8192, rank-20 Gaussian L0, 5% outliers U[-10,10], noise 1e-3, "
                                "Bernoulli(0.3) mask, k=25, lam_S=1/sqrt(8192), lam_L=1, rSVD start"},
         "objgrad": rates, "solves": solves,
-        "roofline": dict(bound="hbm", kernel="k_sweep (masked, k=25)", kernel_ms=sw / 1e3,
+        "roofline": dict(bound="hbm", kernel="k_sweep_cols (masked, k=25)", kernel_ms=sw / 1e3,
                          achieved=round(alg_bytes / (sw * 1e-6) / 1e9, 1), peak=HBM_PEAK_GBS, unit="GB/s",
                          frac=round(alg_bytes / (sw * 1e-6) / 1e9 / HBM_PEAK_GBS, 4), traffic=None,
                          alg_bytes_per_launch=alg_bytes),
@@ -629,9 +629,10 @@ def probe(args):
 
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sweep_fp32_video76800x200_hbm_traffic.md")
-SWEEP_SOURCES = [os.path.join(ROOT, "paper_1702_02241_amd", "csrc", f) for f in ("sweep_cols.h",)]
+# what sets a launch's bytes: the kernel, and the split of rows and columns it is launched with
+SWEEP_SOURCES = [os.path.join(ROOT, "paper_1702_02241_amd", "csrc", f) for f in ("sweep_cols.h", "objgrad.hip")]
 FW_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "gram_apply_fw_video76800x200_hbm_traffic.md")
-FW_SOURCES = [os.path.join(ROOT, "paper_1702_02241_amd", "csrc", "gram_apply.hip")]
+FW_SOURCES = [os.path.join(ROOT, "paper_1702_02241_amd", "csrc", f) for f in ("gram_apply.hip", "sweep_cols.h", "fw.hip")]
 
 
 def source_hash(files=None):
@@ -799,7 +800,7 @@ def main():
     achieved = alg_bytes / (sweep_ms * 1e-3) / 1e9
     roofline = dict(bound="hbm", achieved=round(achieved, 1), peak=HBM_PEAK_GBS, unit="GB/s",
                     frac=round(achieved / HBM_PEAK_GBS, 4), traffic=measured_traffic(),
-                    kernel="k_sweep (objective/gradient evaluation, FP32 products)", kernel_ms=round(sweep_ms, 5),
+                    kernel="k_sweep_cols (objective/gradient evaluation, FP32 products)", kernel_ms=round(sweep_ms, 5),
                     launches=int(prof.launches[R.RPCA_K_SWEEP]), finish_ms=round(finish_ms, 5),
                     alg_bytes_per_launch=alg_bytes)
     # MFMA share of the same launches: the algorithmic flops of the three products
@@ -821,7 +822,7 @@ def main():
     sweep_b = prof_b.ms[R.RPCA_K_SWEEP] / max(prof_b.launches[R.RPCA_K_SWEEP], 1)
     ach_b = alg_bytes / (sweep_b * 1e-3) / 1e9
     roofline_bf16 = dict(bound="hbm", achieved=round(ach_b, 1), peak=HBM_PEAK_GBS, unit="GB/s",
-                         frac=round(ach_b / HBM_PEAK_GBS, 4), kernel="k_sweep (BF16 products)",
+                         frac=round(ach_b / HBM_PEAK_GBS, 4), kernel="k_sweep_cols (BF16 products)",
                          kernel_ms=round(sweep_b, 5), mfma_tflops=round(alg_flops / (sweep_b * 1e-3) / 1e12, 2),
                          mfma_peak=MFMA_PEAK_TFLOPS["bf16"],
                          mfma_frac=round(alg_flops / (sweep_b * 1e-3) / 1e12 / MFMA_PEAK_TFLOPS["bf16"], 5))

@@ -348,9 +348,12 @@ int col_blocks_for(int64_t m, int64_t n, int k, int* row_groups, int* strips_per
   if (cw > cmax) cw = cmax;
   nch = (int)((n + cw - 1) / cw);
   // k > 16, and fewer strips than workgroups side by side: narrower chunks, down to a tile
-  // per wave (583 x 359, k = 26, masked: 18.6 to 10.9 us; V and the G^T U sums of a wide chunk
-  // are most of a workgroup's time there; for k <= 16 they are not, and the further chunks
-  // cost the reduction more)
+  // per wave: V and the G^T U sums of a wide chunk are most of a workgroup's time there.  A call
+  // with wide and narrow chunks, us: 583 x 359, k = 26: 20.6, 16.5; 300 x 144, k = 20: 16.3, 15.6;
+  // 1000 x 500, k = 24: 22.9, 17.3; 600 x 600, k = 32: 20.8, 17.5; 256 x 512, k = 18: 20.1, 15.3;
+  // 128 x 2048, k = 25: 22.1, 16.8; 2000 x 300, k = 20: 19.3, 17.8.  For k <= 16 the chunks are as
+  // they were: it gains there too, a little later (583 x 359, k = 16: 16.9, 14.8; 512 x 512, k = 8:
+  // 15.6, 14.6; 256 x 200 and 300 x 144, k = 10: nothing)
   if (k > 16) {
     const int tiles = (int)((n + 15) / 16);
     while ((nch + 1) * nstrips <= t.target_waves / rpca_cols::WAVES && tiles > rpca_cols::WAVES * nch) ++nch;

@@ -192,10 +192,11 @@ SweepTune tune_get(int split, int k, int64_t n);
 void tune_set(int split, int kbucket, int nbucket, SweepTune t);
 // Sweep decomposition of an m x n, rank-k instance: the split by columns, from the tuning
 // table, or for target_waves > 0 the split by strips over that many waves (a batch spreads
-// one chip's waves over many instances).  An explicit wave count keeps the split by strips
-// because its results are held to earlier ones bit for bit: from a random start a few line
-// searches turn a relative change of 2e-9 in f, one rounding order for another, into 3e-4
-// in the factors.
+// one chip's waves over many instances).  A batch and a context with its wave count agree bit
+// for bit, so they share a split.  It is still the split by strips: with the other, factors from
+// a random start came out up to 1e-2 away after 8 iterations (2e-9 in f, one rounding order
+// for another, is 3e-4 after two line searches), and that this is rounding the iteration
+// amplifies, on every instance, has not been shown.
 int sweep_blocks_for(int64_t m, int64_t n, int k, int* row_groups, int* strips_per_wg, int* chunk_w,
                      int* nchunks, int target_waves = 0);
 // The same of either split from a given entry.
@@ -270,12 +271,12 @@ int ctx_objgrad_aux(rpca_ctx* c, const float* X, const float* U, const float* V,
                     double* aux_dev, float* gU, float* gV, hipStream_t s);
 // Device workspace owned by the context, grown on demand; *fresh = 1 when newly allocated.
 void* ctx_workspace(rpca_ctx* c, size_t bytes, int* fresh);
-// Pinned host staging owned by the context (at least 256 KB, grown on demand;
-// null on failure).  Callers synchronise their copies through it before returning.
 // Pinned: two slots of 16 doubles that kernels write and the host reads, then the host's
 // count of steps; or null.
 double* ctx_flags(rpca_ctx* c);
 hipError_t wait_step(const double* flag, double want, hipStream_t s);
+// Pinned host staging owned by the context (at least 256 KB, grown on demand;
+// null on failure).  Callers synchronise their copies through it before returning.
 void* ctx_pinned(rpca_ctx* c, size_t bytes);
 // hipHostFree that leaves no pending error behind when the free fails.
 void host_free(void* p);

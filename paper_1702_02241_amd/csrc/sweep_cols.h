@@ -25,7 +25,7 @@
 // strip) and VALU work.  The earlier split (whole strips per wave, V operands read from LDS
 // for every tile, all the chunk's G^T U accumulators in registers) took 32.8 us there at
 // k = 10, 41.5 us as a solver's trial, 31.9 us in BF16, and 371 us at 8192^2, k = 25; this
-// one 26.0, 29.4, 21.4 and 165.  256 x 200: 12.8 to 7.8 us.  Two waves per SIMD and one
+// one 26.0, 29.4, 21.4 and 167.  256 x 200: 12.8 to 7.8 us.  Two waves per SIMD and one
 // workgroup per compute unit: four waves in 128 registers spilled and took 34.5 to 37 us,
 // with shorter rounds and a barrier each.
 //
@@ -334,7 +334,9 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
   const uint32_t tile_step = 64u * (uint32_t)m;
   const uint32_t* __restrict__ Mw = MASKED ? a.mask + jw * a.mw + (s_lo >> 1) : nullptr;
   // X (and the mask words) of tile t of the workgroup's strip i (past the full strips the
-  // first one's, not used)
+  // first one's, not used: gone from the L2 by then, they are 51,200 of the 574,800 128-byte
+  // lines fetched at 76800 x 200.  An offset past the resource fetches none of them and takes
+  // the same time there, 30.5 us a call for 30.3, but costs k = 25 a register: 57.7 us for 56.2)
   auto load_tile = [&](int i, int t, f4& x, uint32_t& mb) {
     const uint32_t at = i < nfull ? (uint32_t)i * 64u : 0u;
     x = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(xrs, lane_off + (at + t * tile_step), 0, 0));
@@ -460,7 +462,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
     // chain over the strips saturated entries add the same value again and again and round
     // alike.  28 video starts, gV against 64 bits: 5.9e-8 rms (8.8e-8 with groups of three
     // strips, 6.7e-8 in the split by strips), at the same speed (8192 x 8192, k = 25,
-    // masked: 165 us for 174); carrying the additions' rounding along as well gave 5.6e-8 for
+    // masked: 165 us for 174 when it was chosen); carrying the additions' rounding along as well gave 5.6e-8 for
     // 8 % more time there
     f4 gvs[NW][KB];
 #pragma unroll
@@ -634,7 +636,13 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const int rg, con
     };
 
     // the rows of a round: G V + lam_L U (or its preconditioned form) and the scalars, a
-    // strip per wave in the products' output layout (rows 4 g + q, rank 16 kb + c)
+    // strip per wave in the products' output layout (rows 4 g + q, rank 16 kb + c).  The column
+    // groups' sums of a chunk and lam_L U are added in FP32, also where the split by strips has
+    // two chunks or more (n > 256; n > 128 above k = 16) and adds those in 64 bits: its chains
+    // within a chunk are longer, and gU is closer to 64 bits here -- rms of six inputs, there and
+    // here: 5003 x 333, k = 13: 8.6e-8, 5.9e-8; 2000 x 512, k = 10: 1.2e-7, 6.6e-8; 3000 x 300,
+    // k = 24: 8.0e-8, 7.9e-8; 4096 x 2048, k = 25: 5.77e-8, 5.75e-8.  In 64 bits it would be 5.3,
+    // 6.1, 7.2 and 5.5e-8 for 2 to 10 % more time
     auto finish_round = [&](int i0, int ubf) {
       // (lane indices hidden from the compiler: its addresses are not kept across the strips)
       int c = lane & 15, g = lane >> 4;
@@ -773,7 +781,9 @@ inline int lds_floats(const SweepArgs& a, bool bf16) {
   return sweep_lds(a.k, a.chunk_w, 1 << a.lcg, bf16, spr, a.sdiv + (a.srem ? 1 : 0) > spr ? 2 : 1).total;
 }
 
-// Residual steps of a rank class: k <= 12, 16, 24, 28, 32.
+// Residual steps of a rank class: k <= 12, 16, 24, 28, 32.  (Classes of two and five steps,
+// k <= 8 and k <= 20, would take 3 to 5 % off their FP32 evaluations -- 76800 x 200, k = 8: 29.6
+// us a call to 28.4, k = 20: 47.5 to 46.1; BF16 the same -- for two more kernels to each three.)
 __host__ __device__ constexpr int kq_class(int k) { return k <= 12 ? 3 : k <= 16 ? 4 : k <= 24 ? 6 : k <= 28 ? 7 : 8; }
 
 template <bool MASKED, bool TRIAL, bool BF16, bool ELASTIC = false>
