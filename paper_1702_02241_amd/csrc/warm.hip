@@ -9,10 +9,12 @@
 // matrix unit, one block of 16 K values ahead of the products: no LDS staging and
 // no barrier in the K loop.  When the output has few tiles K is split over the
 // waves of a workgroup (summed through LDS) and over workgroups (partials summed
-// by a second kernel), always in a fixed order, so every result is bitwise
+// by a second kernel), or, with K in order, the tile's rows over the waves; always in a
+// fixed order, so every result is bitwise
 // reproducible.  The epilogue adds a bias, applies ReLU or gates by a previous
-// activation (the ReLU derivative in the backward pass).  At most four rows
-// (one window's prediction) take a matrix-vector kernel instead.
+// activation (the ReLU derivative in the backward pass).  Products of at most four rows
+// (one window's prediction) take a matrix-vector kernel instead, but for the first layer of a
+// training step.
 
 #include <hip/hip_runtime.h>
 #include <math.h>
